@@ -12,10 +12,11 @@ namespace svmx {
 hipError_t launch_gram(const float *X, int64_t n, int64_t d, float gamma, float *G, int64_t ld, hipStream_t s);
 hipError_t launch_kernel_rows(const float *X, int64_t n, int64_t d, double gamma, const int64_t *rows, int64_t r,
                               float *out, hipStream_t s);
-// Rows of X scaled by powers of two and split into two fp16 halves (gram_split.hip): hi and lo
-// [n][dp] (dp = d rounded up to 32, zero padded), the row scales and the row norms.
+// Rows of X scaled by powers of two and split into two fp16 halves (gram_split.hip): row r is
+// rows[r * 2 dp ..], for each 32 features its hi halves, then its lo halves (128 bytes; dp = d
+// rounded up to 32, zero padded), with the row scales and the row norms.
 struct SplitX {
-  _Float16 *hi, *lo;
+  _Float16 *rows;
   float *scale, *nrm;
   int64_t dp;
 };

@@ -10,7 +10,7 @@
 // fp32 product on the 157 TFLOP/s path; measured against the fp64 difference form, the values
 // are as accurate as those of the fp32 MFMA kernel.  The row norms are fp64 sums of the fp32
 // inputs.
-#include "common.hpp"
+#include "split_tile.hpp"
 #include "tile_order.hpp"
 #include "tile_store.hpp"
 
@@ -18,17 +18,10 @@
 
 namespace svmx {
 
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-constexpr int ST = 128;   // tile edge (rows and columns)
-constexpr int SKS = 32;   // k per stage: one MFMA K
-constexpr int SBS = 256;  // 4 waves, 2x2 over the tile, 64x64 each
-
 int64_t split_pitch(int64_t d) { return (d + SKS - 1) / SKS * SKS; }
 
-// Scratch of the split Gram: hi and lo halves [n][dp] (dp = d rounded up to 32, zero padded),
-// the power-of-two row scales and the row norms.
+// Scratch of the split rows: [n][dp / 32][hi 32 | lo 32] halves (dp = d rounded up to 32, zero
+// padded), the power-of-two row scales and the row norms.
 int64_t gram_split_scratch_bytes(int64_t n, int64_t d) {
   const int64_t dp = split_pitch(d);
   return 2 * (2 * n * dp) + 8 * n + 256;
@@ -38,205 +31,121 @@ SplitX split_views(void *scratch, int64_t n, int64_t d) {
   SplitX s;
   s.dp = split_pitch(d);
   char *p = static_cast<char *>(scratch);
-  s.hi = reinterpret_cast<_Float16 *>(p);
-  s.lo = s.hi + n * s.dp;
-  s.scale = reinterpret_cast<float *>(s.lo + n * s.dp);
+  s.rows = reinterpret_cast<_Float16 *>(p);
+  s.scale = reinterpret_cast<float *>(s.rows + 2 * n * s.dp);
   s.nrm = s.scale + n;
   return s;
 }
 
-// One wave per row: s = 2^e with max|x| < 2^e, h = fp16(x / s), l = fp16(x / s - h), and the
-// norm |x|^2 as an fp64 sum rounded to fp32.
-__global__ void __launch_bounds__(256) gram_split_k(const float *__restrict__ X, int64_t n, int64_t d, SplitX s) {
-  const int lane = threadIdx.x & 63;
-  const int64_t waves = (int64_t)gridDim.x * 4;
-  for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < n; r += waves) {
-    const float *x = X + r * d;
+// s = 2^e with max|x| < 2^e, h = fp16(x / s), l = fp16(x / s - h), and the norm |x|^2 as an fp64
+// sum rounded to fp32.  gs lanes a row (a power of two covering its chunks of 8 features, at most
+// 64): each lane reads 8 consecutive features at once (two 16-byte loads, whatever the alignment
+// of the row) and writes 16 bytes of each half, so every store instruction of a wave fills whole
+// 128-byte lines.  Up to SPLIT_KEEP chunks a lane stay in registers between the two passes.
+// Bound by reading X and writing as many bytes: 20,000 x 784 20 us, against 34 us with one
+// feature a lane (2-byte stores).
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int SPLIT_KEEP = 4;
+
+__device__ __forceinline__ void split_chunk_load(const float *__restrict__ x, int64_t d, int64_t k, float (&v)[8]) {
+  if (k + 8 <= d) {
+    const f4u a = *reinterpret_cast<const f4u *>(x + k), b = *reinterpret_cast<const f4u *>(x + k + 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = a[e];
+      v[4 + e] = b[e];
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = k + e < d ? x[k + e] : 0.f;
+  }
+}
+
+__device__ __forceinline__ void split_chunk_store(_Float16 *__restrict__ row, int64_t k, float inv, const float (&v)[8]) {
+  h8 h, l;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float w = v[e] * inv;  // exact (power of two)
+    h[e] = (_Float16)w;
+    l[e] = (_Float16)(w - (float)h[e]);  // w - h is exact in fp32
+  }
+  _Float16 *p = row + (k >> 5) * 64 + (k & 31);
+  *reinterpret_cast<h8 *>(p) = h;
+  *reinterpret_cast<h8 *>(p + 32) = l;
+}
+
+__global__ void __launch_bounds__(256) gram_split_k(const float *__restrict__ X, int64_t n, int64_t d, SplitX s, int gs) {
+  const int g = threadIdx.x & (gs - 1);
+  const int64_t chunks = s.dp >> 3;
+  const int64_t groups = (int64_t)gridDim.x * (256 / gs);
+  // every lane of a wave runs the same number of rounds (the reductions cross lanes)
+  for (int64_t r0 = (int64_t)blockIdx.x * (256 / gs); r0 < n; r0 += groups) {
+    const int64_t r = r0 + threadIdx.x / gs;
+    const bool in = r < n;
+    const float *x = X + (in ? r : 0) * d;
+    float v[SPLIT_KEEP][8];
     float m = 0.f;
     double q = 0.0;
-    for (int64_t k = lane; k < d; k += 64) {
-      const float v = x[k];
-      m = fmaxf(m, fabsf(v));
-      q = __builtin_fma((double)v, (double)v, q);
-    }
+    auto take = [&](const float (&c)[8]) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
+      for (int e = 0; e < 8; ++e) {
+        m = fmaxf(m, fabsf(c[e]));
+        q = __builtin_fma((double)c[e], (double)c[e], q);
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < SPLIT_KEEP; ++i)
+      if (g + i * gs < chunks) split_chunk_load(x, d, 8 * (int64_t)(g + i * gs), v[i]);
+#pragma unroll
+    for (int i = 0; i < SPLIT_KEEP; ++i)
+      if (g + i * gs < chunks) take(v[i]);
+    for (int64_t c = g + (int64_t)SPLIT_KEEP * gs; c < chunks; c += gs) {
+      float w[8];
+      split_chunk_load(x, d, 8 * c, w);
+      take(w);
+    }
+    for (int o = gs >> 1; o > 0; o >>= 1) {
       m = fmaxf(m, __shfl_xor(m, o));
       q += __shfl_xor(q, o);
     }
+    if (!in) continue;
     int e = 0;
     if (m > 0.f) (void)frexpf(m, &e);  // m = f 2^e, f in [0.5, 1)
     const float inv = ldexpf(1.0f, -e);
-    _Float16 *hr = s.hi + r * s.dp, *lr = s.lo + r * s.dp;
-    for (int64_t k = lane; k < s.dp; k += 64) {
-      const float v = k < d ? x[k] * inv : 0.f;  // exact (power of two)
-      const _Float16 h = (_Float16)v;
-      hr[k] = h;
-      lr[k] = (_Float16)(v - (float)h);  // v - h is exact in fp32
+    _Float16 *row = s.rows + r * 2 * s.dp;
+#pragma unroll
+    for (int i = 0; i < SPLIT_KEEP; ++i)
+      if (g + i * gs < chunks) split_chunk_store(row, 8 * (int64_t)(g + i * gs), inv, v[i]);
+    for (int64_t c = g + (int64_t)SPLIT_KEEP * gs; c < chunks; c += gs) {
+      float w[8];
+      split_chunk_load(x, d, 8 * c, w);
+      split_chunk_store(row, 8 * c, inv, w);
     }
-    if (lane == 0) {
+    if (g == 0) {
       s.scale[r] = ldexpf(1.0f, e);
       s.nrm[r] = (float)q;
     }
   }
 }
 
-// LDS stage: [slab: A hi, A lo, B hi, B lo][k chunk of 8][row] of 16-byte vectors, so the 16
-// lanes that read one MFMA operand read 256 contiguous bytes.
-struct SplitStage {
-  h8 v[4][SKS / 8][ST];
-};
-
-// This thread's share of one stage: rows t/2 of the A and B tiles, k chunks 2*(t%2), +1.
-__device__ __forceinline__ void split_load(const SplitX &s, int64_t n, int64_t i0, int64_t j0, int64_t k0, h8 (&r)[8]) {
-  const int t = threadIdx.x;
-  const int row = t >> 1, kq = (t & 1) * 2;
-#pragma unroll
-  for (int sl = 0; sl < 4; ++sl) {
-    const int64_t g = (sl < 2 ? i0 : j0) + row;
-    const _Float16 *base = (sl & 1) ? s.lo : s.hi;
-    if (g < n) {
-      const h8 *p = reinterpret_cast<const h8 *>(base + g * s.dp + k0) + kq;
-      r[2 * sl] = p[0];
-      r[2 * sl + 1] = p[1];
-    } else {
-      r[2 * sl] = (h8){};
-      r[2 * sl + 1] = (h8){};
-    }
-  }
-}
-
-__device__ __forceinline__ void split_store(SplitStage &S, const h8 (&r)[8]) {
-  const int t = threadIdx.x;
-  const int row = t >> 1, kq = (t & 1) * 2;
-#pragma unroll
-  for (int sl = 0; sl < 4; ++sl) {
-    S.v[sl][kq][row] = r[2 * sl];
-    S.v[sl][kq + 1][row] = r[2 * sl + 1];
-  }
-}
-
 // One 128x128 tile of the upper triangle per workgroup; workgroup b runs on XCD b % 8 and takes
 // tile b / 8 of that XCD's contiguous share of the super-tile order (tile_order.hpp), so the
 // tiles an XCD holds at once share their row and column slabs in its L2.  An off-diagonal
-// tile is stored twice, as itself and mirrored.  The stores are non-temporal: the Gram is not
-// read again by this kernel, so its lines should not displace the operand slabs from L2
-// (measured: 12.0 -> 9.8 ms for the 60,000 x 784 Gram, 1.35 -> 1.16 ms at 20,000 x 784,
-// 3.67 -> 3.30 ms at 50,000 x 128, 12.6 -> 12.2 ms at 100,000 x 32).  Lane l of an MFMA holds
-// D[4*(l/16) + e][l%16] of each 16x16 block.
-template <bool STORE4>
-__global__ void __launch_bounds__(SBS) gram_rbf_f16x3(SplitX s, int64_t n, float c, float *__restrict__ G, int64_t ld,
-                                                      int64_t nt, int64_t ntiles) {
-  __shared__ SplitStage S[2];
-  __shared__ float sA[ST], sB[ST], nA[ST], nB[ST];
-  const int64_t per_xcd = (ntiles + 7) / 8;
-  const int64_t b = (int64_t)blockIdx.x;
-  const int64_t lin = (b % 8) * per_xcd + b / 8;
-  if (lin >= ntiles) return;
-  int64_t ti, tj;
-  upper_tile_super(lin, nt, ti, tj);
-  const int64_t i0 = ti * ST, j0 = tj * ST;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wm = w >> 1, wn = w & 1;
-  const int kq = lane >> 4, r16 = lane & 15;
-
-  if (threadIdx.x < ST) {
-    const int64_t gi = i0 + threadIdx.x, gj = j0 + threadIdx.x;
-    sA[threadIdx.x] = gi < n ? s.scale[gi] : 0.f;
-    nA[threadIdx.x] = gi < n ? s.nrm[gi] : 0.f;
-    sB[threadIdx.x] = gj < n ? s.scale[gj] : 0.f;
-    nB[threadIdx.x] = gj < n ? s.nrm[gj] : 0.f;
-  }
-  v4f acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int bb = 0; bb < 4; ++bb) acc[a][bb] = (v4f){0.f, 0.f, 0.f, 0.f};
-  h8 r[8];
-  split_load(s, n, i0, j0, 0, r);
-  split_store(S[0], r);
-  __syncthreads();
-  const int64_t stages = s.dp / SKS;
-  for (int64_t st = 0; st < stages; ++st) {
-    const int cur = (int)(st & 1);
-    if (st + 1 < stages) split_load(s, n, i0, j0, (st + 1) * SKS, r);
-    h8 ah[4], al[4], bh[4], bl[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      ah[a] = S[cur].v[0][kq][wm * 64 + a * 16 + r16];
-      al[a] = S[cur].v[1][kq][wm * 64 + a * 16 + r16];
-      bh[a] = S[cur].v[2][kq][wn * 64 + a * 16 + r16];
-      bl[a] = S[cur].v[3][kq][wn * 64 + a * 16 + r16];
-    }
-    // the three products of a block go into one accumulator; each sweep over the 16 blocks
-    // keeps 16 independent MFMAs between two uses of an accumulator
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int bb = 0; bb < 4; ++bb) acc[a][bb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[a], bh[bb], acc[a][bb], 0, 0, 0);
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int bb = 0; bb < 4; ++bb) acc[a][bb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[a], bl[bb], acc[a][bb], 0, 0, 0);
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int bb = 0; bb < 4; ++bb) acc[a][bb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[a], bh[bb], acc[a][bb], 0, 0, 0);
-    if (st + 1 < stages) split_store(S[cur ^ 1], r);
-    __syncthreads();
-  }
-
-  const bool diag = ti == tj;
-  // A diagonal tile holds both K(x_r, x_c) and K(x_c, x_r).  The cross products h.l and l.h
-  // are accumulated in the order of the operand roles, so the two can differ in the last bit;
-  // the upper one (row index <= column index, the role every off-diagonal tile uses) is
-  // mirrored into the lower one through LDS (the stage buffers, free after the loop), so that
-  // K(x_i, x_j) of i < j is always computed with x_i as the row operand.
-  float(*T)[ST] = reinterpret_cast<float(*)[ST]>(&S[0]);
-  static_assert(sizeof(S) >= sizeof(float) * ST * ST, "mirror tile does not fit the stage buffers");
-  float kv[4][4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int lr0 = wm * 64 + a * 16 + 4 * kq;
-    const int64_t gr0 = i0 + lr0;
-#pragma unroll
-    for (int bb = 0; bb < 4; ++bb) {
-      const int lc = wn * 64 + bb * 16 + r16;
-      const int64_t gc = j0 + lc;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        kv[a][bb][e] = (gr0 + e == gc) ? 1.0f : split_rbf(acc[a][bb][e], sA[lr0 + e], sB[lc], nA[lr0 + e], nB[lc], c);
-      if (diag) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) T[lr0 + e][lc] = kv[a][bb][e];
-      }
-    }
-  }
-  if (!diag) {
-    store_tile_128<STORE4>(G, ld, n, i0 + wm * 64, j0 + wn * 64, kq, r16, kv);
-    return;
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < ST * ST; q += SBS) {
-    const int r = q / ST, cc = q % ST;
-    const int64_t gr = i0 + r, gcc = j0 + cc;
-    if (gr < n && gcc < n) __builtin_nontemporal_store(r <= cc ? T[r][cc] : T[cc][r], &G[gr * ld + gcc]);
-  }
-}
-
-// One LDS stage (32 KB, loaded, then multiplied, no register prefetch) instead of two, so four
-// workgroups share a CU instead of two; a diagonal tile writes each upper value to both of its
-// places instead of mirroring through LDS.  Same products in the same order, so the same
-// values.  Short rows are bound by the stores, and four workgroups a CU keep twice as many in
-// flight: 13.9 -> 11.3-11.7 ms at 100,000 x 32 (40 GB), 3.5 -> 3.3 ms at 50,000 x 128.  Long
-// rows are bound by the stage loads and the MFMA schedule, and there the other workgroups'
-// products cover each one's loads better than one stage of register prefetch in two:
-// 1.34 -> 1.12 ms at 20,000 x 784, 10.95 -> 9.73 ms at 60,000 x 784, 0.66 -> 0.53 ms at
-// 20,000 x 256.  The two-stage kernel remains for a Gram whose row pitch or base does not
-// allow float4 stores.
-__global__ void __launch_bounds__(SBS, 4) gram_rbf_f16x3_lds1(SplitX s, int64_t n, float c, float *__restrict__ G,
-                                                             int64_t ld, int64_t nt, int64_t ntiles, int64_t sup) {
-  __shared__ SplitStage S[1];
+// tile is stored twice, as itself and mirrored.  Lane l of an MFMA holds D[4*(l/16) + e][l%16]
+// of each 16x16 block.
+// Long rows are bound by the matrix cores (20,000 x 784: the products alone 0.66 ms at the
+// 1,450 TFLOP/s the stage loop reaches, 0.91 ms in all against 1.16 ms with stages staged through
+// registers; 60,000 x 784 7.7 against 9.8 ms), short ones by the stores (100,000 x 32: 40 GB in
+// 7.0 ms).  Four workgroups a CU: one's products run under the others' loads and stores (three:
+// 50,000 x 128 2.07 instead of 2.01 ms, 60,000 x 784 7.88 instead of 7.70).
+// In a diagonal tile the cross products h.l and l.h are accumulated in the order of the operand
+// roles, so K(x_r, x_c) and K(x_c, x_r) can differ in the last bit; the upper one (row index <=
+// column index, the role every off-diagonal tile uses) is written to both places, so that
+// K(x_i, x_j) of i < j is always computed with x_i as the row operand.
+template <bool NT>
+__global__ void __launch_bounds__(SBS, 4) gram_rbf_f16x3(SplitX s, int64_t n, float c, float *__restrict__ G, int64_t ld,
+                                                      int64_t nt, int64_t ntiles, int64_t sup) {
+  __shared__ SplitStage S;
   __shared__ float sA[ST], sB[ST], nA[ST], nB[ST];
   const int64_t per_xcd = (ntiles + 7) / 8;
   const int64_t b = (int64_t)blockIdx.x;
@@ -244,8 +153,10 @@ __global__ void __launch_bounds__(SBS, 4) gram_rbf_f16x3_lds1(SplitX s, int64_t 
   if (lin >= ntiles) return;
   int64_t ti, tj;
   upper_tile_super(lin, nt, ti, tj, sup);
-  const int64_t i0 = ti * ST, j0 = tj * ST;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  // (uniform by construction; said so, the store addresses stay in scalar registers)
+  const int64_t i0 = (int64_t)__builtin_amdgcn_readfirstlane((int)ti) * ST;
+  const int64_t j0 = (int64_t)__builtin_amdgcn_readfirstlane((int)tj) * ST;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = w >> 1, wn = w & 1;
   const int kq = lane >> 4, r16 = lane & 15;
   if (threadIdx.x < ST) {
@@ -255,42 +166,13 @@ __global__ void __launch_bounds__(SBS, 4) gram_rbf_f16x3_lds1(SplitX s, int64_t 
     sB[threadIdx.x] = gj < n ? s.scale[gj] : 0.f;
     nB[threadIdx.x] = gj < n ? s.nrm[gj] : 0.f;
   }
+  const char *src[SCH];  // waves 0 and 1 load the rows of A, 2 and 3 those of B (past the end: the last row again)
+#pragma unroll
+  for (int q = 0; q < SCH; ++q)
+    src[q] = split_src(s, min<int64_t>((w < 2 ? i0 : j0) + ((w & 1) * SCH + q) * 8 + (lane >> 3), n - 1));
   v4f acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int bb = 0; bb < 4; ++bb) acc[a][bb] = (v4f){0.f, 0.f, 0.f, 0.f};
-  const int64_t stages = s.dp / SKS;
-  for (int64_t stg = 0; stg < stages; ++stg) {
-    {
-      h8 r[8];
-      split_load(s, n, i0, j0, stg * SKS, r);
-      if (stg > 0) __syncthreads();  // the previous stage's operands have been read
-      split_store(S[0], r);
-    }
-    __syncthreads();
-    h8 ah[4], al[4], bh[4], bl[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      ah[a] = S[0].v[0][kq][wm * 64 + a * 16 + r16];
-      al[a] = S[0].v[1][kq][wm * 64 + a * 16 + r16];
-      bh[a] = S[0].v[2][kq][wn * 64 + a * 16 + r16];
-      bl[a] = S[0].v[3][kq][wn * 64 + a * 16 + r16];
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int bb = 0; bb < 4; ++bb) acc[a][bb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[a], bh[bb], acc[a][bb], 0, 0, 0);
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int bb = 0; bb < 4; ++bb) acc[a][bb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[a], bl[bb], acc[a][bb], 0, 0, 0);
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int bb = 0; bb < 4; ++bb) acc[a][bb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[a], bh[bb], acc[a][bb], 0, 0, 0);
-  }
-  const bool diag = ti == tj;
+  split_tile(S, src, s.dp / SKS, wm, wn, acc);
+  const bool diag = i0 == j0;
   float kv[4][4][4];
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
@@ -314,14 +196,17 @@ __global__ void __launch_bounds__(SBS, 4) gram_rbf_f16x3_lds1(SplitX s, int64_t 
       }
     }
   }
-  if (!diag) store_tile_128<true>(G, ld, n, i0 + wm * 64, j0 + wn * 64, kq, r16, kv);
+  if (!diag) store_tile_128<NT>(G, ld, n, i0 + wm * 64, j0 + wn * 64, kq, r16, kv);
 }
 
 hipError_t launch_split_rows(const float *X, int64_t n, int64_t d, const SplitX &s, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  int64_t pb = (n + 3) / 4;
+  int gs = 1;  // lanes a row
+  while (gs < 64 && (int64_t)gs * 8 < s.dp) gs <<= 1;
+  const int64_t per = 256 / gs;
+  int64_t pb = (n + per - 1) / per;
   if (pb > 8192) pb = 8192;
-  hipLaunchKernelGGL(gram_split_k, dim3((unsigned)pb), dim3(256), 0, st, X, n, d, s);
+  hipLaunchKernelGGL(gram_split_k, dim3((unsigned)pb), dim3(256), 0, st, X, n, d, s, gs);
   return hipGetLastError();
 }
 
@@ -335,16 +220,21 @@ hipError_t launch_gram_split(const float *X, int64_t n, int64_t d, float gamma, 
   const int64_t grid = ((ntiles + 7) / 8) * 8;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
   const float c = -gamma * 1.4426950408889634f;
-  const bool st4 = (ld % 4 == 0) && ((reinterpret_cast<uintptr_t>(G) & 15) == 0);
-  if (st4) {
-    // super-tiles of 32 x 32 tiles for rows of up to 128 features, whose build is bound by its
-    // stores (measured: 8.7 -> 7.7 ms at 100,000 x 32, 16.6 -> 13.2 ms at 130,000 x 32, 2.44 ->
-    // 2.37 ms at 50,000 x 128), 8 x 8 for longer rows (1.09 against 1.25 ms at 20,000 x 784)
-    const int64_t sup = s.dp <= 4 * SKS ? 32 : 8;
-    hipLaunchKernelGGL(gram_rbf_f16x3_lds1, dim3((unsigned)grid), dim3(SBS), 0, st, s, n, c, G, ld, nt, ntiles, sup);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL((gram_rbf_f16x3<false>), dim3((unsigned)grid), dim3(SBS), 0, st, s, n, c, G, ld, nt, ntiles);
+  // Non-temporal stores where the Gram is larger than the 256 MB Infinity Cache (it is not read
+  // again here, so its lines should not displace the operand slabs from L2: 60,000 x 784 7.7
+  // against 8.3 ms, 50,000 x 128 2.0 against 2.3); a smaller one stays in the caches, for the
+  // solver to read (8,000 x 64 81 against 93 us, 10,000 x 64, 400 MB, the same), and rows that
+  // are not 16-byte aligned need L2 to put their lines together (tile_store.hpp).
+  const bool aligned = (ld % 4 == 0) && ((reinterpret_cast<uintptr_t>(G) & 15) == 0);
+  const bool nt_store = aligned && 4.0 * (double)n * (double)ld > 256e6;
+  // super-tiles of 32 x 32 tiles for rows of up to 128 features, whose build is bound by its
+  // stores (measured: 8.7 -> 7.7 ms at 100,000 x 32, 16.6 -> 13.2 ms at 130,000 x 32, 2.44 ->
+  // 2.37 ms at 50,000 x 128), 8 x 8 for longer rows (1.09 against 1.25 ms at 20,000 x 784)
+  const int64_t sup = s.dp <= 4 * SKS ? 32 : 8;
+  if (nt_store)
+    hipLaunchKernelGGL(gram_rbf_f16x3<true>, dim3((unsigned)grid), dim3(SBS), 0, st, s, n, c, G, ld, nt, ntiles, sup);
+  else
+    hipLaunchKernelGGL(gram_rbf_f16x3<false>, dim3((unsigned)grid), dim3(SBS), 0, st, s, n, c, G, ld, nt, ntiles, sup);
   return hipGetLastError();
 }
 

@@ -12,13 +12,11 @@
 //    Gram build (predict_f16x3); `gram_mfma = SVM_MFMA_F32` keeps the fp32 kernel.
 // 3. predict_final: dec = sum over splits (fixed order) - b.
 // Results are deterministic: no atomics touch values.
-#include "common.hpp"
+#include "split_tile.hpp"
 
 #include <math.h>
 
 namespace svmx {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int PT = 128;        // tile edge
 constexpr int PKC = 16;        // k per LDS stage
@@ -214,57 +212,10 @@ __global__ void __launch_bounds__(PBS) predict_mfma_k(const float *__restrict__ 
   if (threadIdx.x < PT && q0 + threadIdx.x < m) part[(int64_t)split * m + q0 + threadIdx.x] = row_acc;
 }
 
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-constexpr int PKS = 32;  // k per stage of the split kernel (one MFMA K)
-
-struct PredStage {
-  h8 v[4][PKS / 8][PT];  // [A hi, A lo, B hi, B lo][k chunk of 8][row]
-};
-
-// This thread's share of one stage: rows t/2 of the test tile (A, rows q0..) and of the
-// support-vector tile (B, rows sv_row[s0..]), k chunks 2*(t%2), +1.  Rows past the end are 0.
-__device__ __forceinline__ void pred_split_load(const SplitX &st, const SplitX &sx, int64_t m, int64_t q0,
-                                                const int32_t *__restrict__ sv_row, int64_t nsv, int64_t s0, int64_t k0,
-                                                h8 (&r)[8]) {
-  const int t = threadIdx.x;
-  const int row = t >> 1, kq = (t & 1) * 2;
-  const int64_t qa = q0 + row, qb = s0 + row;
-  const bool va = qa < m, vb = qb < nsv;
-  const int64_t rb = vb ? (int64_t)sv_row[qb] : 0;
-#pragma unroll
-  for (int sl = 0; sl < 4; ++sl) {
-    const bool v = sl < 2 ? va : vb;
-    const SplitX &S = sl < 2 ? st : sx;
-    const int64_t g = sl < 2 ? qa : rb;
-    const _Float16 *base = (sl & 1) ? S.lo : S.hi;
-    if (v) {
-      const h8 *p = reinterpret_cast<const h8 *>(base + g * S.dp + k0) + kq;
-      r[2 * sl] = p[0];
-      r[2 * sl + 1] = p[1];
-    } else {
-      r[2 * sl] = (h8){};
-      r[2 * sl + 1] = (h8){};
-    }
-  }
-}
-
-__device__ __forceinline__ void pred_split_store(PredStage &S, const h8 (&r)[8]) {
-  const int t = threadIdx.x;
-  const int row = t >> 1, kq = (t & 1) * 2;
-#pragma unroll
-  for (int sl = 0; sl < 4; ++sl) {
-    S.v[sl][kq][row] = r[2 * sl];
-    S.v[sl][kq + 1][row] = r[2 * sl + 1];
-  }
-}
-
 // predict_mfma_k on the split representation: st holds the test rows, sx the training rows
-// (support vectors addressed through sv_row); dot = acc * s_q * s_j.  One LDS stage (loaded,
-// then multiplied) instead of two with register prefetch, so three workgroups share a CU
-// instead of two and each one's stage loads run under the others' products; same products in
-// the same order, so the same values.  Measured at 10,000 test rows: 1.41 -> 1.38 ms with
-// 15,016 support vectors of 784 features, 0.55 -> 0.44 ms with 20,000 of 128, 0.36 -> 0.32 ms
-// with 13,500 of 32.
+// (support vectors gathered through sv_row, rows past the end repeated with coefficient 0);
+// dot = acc * s_q * s_j.  Contraction as in the Gram build (split_tile.hpp), three workgroups a
+// CU.
 __global__ void __launch_bounds__(PBS, 3) predict_f16x3_k(SplitX st, int64_t m, SplitX sx,
                                                        const PredPair *__restrict__ pairs,
                                                        const int32_t *__restrict__ sv_row_all,
@@ -277,14 +228,14 @@ __global__ void __launch_bounds__(PBS, 3) predict_f16x3_k(SplitX st, int64_t m, 
   const int32_t *sv_row = sv_row_all + pp.sv_off;
   const double *sv_coef = sv_coef_all + pp.sv_off;
   double *part = part_all + pp.part_off;
-  __shared__ PredStage S[1];
+  __shared__ SplitStage S;
   __shared__ float sA[PT], nA[PT], sB[PT], nB[PT];
   __shared__ double cB[PT];
   __shared__ double rs[2][PT];
   const int64_t nsv = sv_count[blockIdx.z];
   const int64_t q0 = (int64_t)blockIdx.x * PT;
   const int split = blockIdx.y;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = w >> 1, wn = w & 1;
   const int kq = lane >> 4, r16 = lane & 15;
   if (threadIdx.x < PT) {
@@ -294,7 +245,6 @@ __global__ void __launch_bounds__(PBS, 3) predict_f16x3_k(SplitX st, int64_t m, 
   }
   double row_acc = 0.0;  // thread t < 128 owns test row q0 + t
   const int64_t ntile = (nsv + PT - 1) / PT;
-  const int64_t stages = st.dp / PKS;
   for (int64_t tile = split; tile < ntile; tile += nsplit) {
     const int64_t s0 = tile * PT;
     if (threadIdx.x < PT) {
@@ -304,36 +254,14 @@ __global__ void __launch_bounds__(PBS, 3) predict_f16x3_k(SplitX st, int64_t m, 
       nB[threadIdx.x] = rr >= 0 ? sx.nrm[rr] : 0.f;
       cB[threadIdx.x] = rr >= 0 ? sv_coef[q] : 0.0;
     }
-    v4f acc[4][4];
+    const char *src[SCH];  // waves 0 and 1 load the test rows, 2 and 3 the support vectors
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) acc[a][b] = (v4f){0.f, 0.f, 0.f, 0.f};
-    for (int64_t sg = 0; sg < stages; ++sg) {
-      {
-        h8 r[8];
-        pred_split_load(st, sx, m, q0, sv_row, nsv, s0, sg * PKS, r);
-        if (sg > 0) __syncthreads();  // the previous stage's operands have been read
-        pred_split_store(S[0], r);
-      }
-      __syncthreads();
-      h8 ah[4], al[4], bh[4], bl[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        ah[a] = S[0].v[0][kq][wm * 64 + a * 16 + r16];
-        al[a] = S[0].v[1][kq][wm * 64 + a * 16 + r16];
-        bh[a] = S[0].v[2][kq][wn * 64 + a * 16 + r16];
-        bl[a] = S[0].v[3][kq][wn * 64 + a * 16 + r16];
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[a], bh[b], acc[a][b], 0, 0, 0);
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[a], bl[b], acc[a][b], 0, 0, 0);
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[a], bh[b], acc[a][b], 0, 0, 0);
-        }
+    for (int q = 0; q < SCH; ++q) {
+      const int64_t r = ((w & 1) * SCH + q) * 8 + (lane >> 3);
+      src[q] = w < 2 ? split_src(st, min<int64_t>(q0 + r, m - 1)) : split_src(sx, sv_row[min<int64_t>(s0 + r, nsv - 1)]);
     }
+    v4f acc[4][4];
+    split_tile(S, src, st.dp / SKS, wm, wn, acc);
     // per test row: sum over this wave's 64 columns (4 blocks x 16 lanes), then the two halves
 #pragma unroll
     for (int a = 0; a < 4; ++a) {

@@ -16,23 +16,24 @@ namespace svmx {
 // wider super-tile (32) keeps on fewer rows of the Gram at a time.
 constexpr int64_t SUPER = 8;
 
-__host__ __device__ inline void upper_tile_super(int64_t lin, int64_t nt, int64_t &ti, int64_t &tj,
-                                                 const int64_t SUPER = svmx::SUPER) {
-  int64_t I = 0, base = 0, r = 0, right = 0;
+__host__ __device__ inline void upper_tile_super(int64_t lin64, int64_t nt64, int64_t &ti, int64_t &tj,
+                                                 const int64_t super = svmx::SUPER) {
+  // A launch has fewer than 2^31 tiles, so 32-bit arithmetic (a 64-bit division costs a hundred
+  // instructions, before the first load of a tile).
+  const uint32_t lin = (uint32_t)lin64, nt = (uint32_t)nt64, S = (uint32_t)super;
+  uint32_t r0 = 0, base = 0, r = 0, right = 0;
   for (;;) {
-    r = nt - SUPER * I < SUPER ? nt - SUPER * I : SUPER;
-    right = nt - SUPER * I - SUPER;
-    if (right < 0) right = 0;
-    const int64_t cnt = r * (r + 1) / 2 + r * right;
+    r = nt - r0 < S ? nt - r0 : S;
+    right = nt - r0 - r;
+    const uint32_t cnt = r * (r + 1) / 2 + r * right;
     if (lin < base + cnt) break;
     base += cnt;
-    ++I;
+    r0 += S;
   }
-  int64_t off = lin - base;
-  const int64_t r0 = SUPER * I;
-  const int64_t dcnt = r * (r + 1) / 2;
+  uint32_t off = lin - base;
+  const uint32_t dcnt = r * (r + 1) / 2;
   if (off < dcnt) {  // diagonal super-tile: row a holds r - a tiles
-    int64_t a = 0;
+    uint32_t a = 0;
     while (off >= r - a) {
       off -= r - a;
       ++a;
@@ -41,18 +42,12 @@ __host__ __device__ inline void upper_tile_super(int64_t lin, int64_t nt, int64_
     tj = r0 + a + off;
     return;
   }
-  off -= dcnt;
-  const int64_t nfull = right / SUPER;  // full-width super-tiles to the right
-  if (off < nfull * r * SUPER) {
-    const int64_t J = off / (r * SUPER), o2 = off % (r * SUPER);
-    ti = r0 + o2 / SUPER;
-    tj = r0 + SUPER + J * SUPER + o2 % SUPER;
-    return;
-  }
-  const int64_t o2 = off - nfull * r * SUPER;
-  const int64_t c = right - nfull * SUPER;  // width of the last, narrower super-tile
+  off -= dcnt;  // only a super-row of full height has tiles to its right
+  const uint32_t J = off / (r * S), nfull = right / S;
+  const uint32_t o2 = off - J * r * S;
+  const uint32_t c = J < nfull ? S : right - nfull * S;  // width of this super-tile (the last may be narrower)
   ti = r0 + o2 / c;
-  tj = r0 + SUPER + nfull * SUPER + o2 % c;
+  tj = r0 + S + J * S + o2 % c;
 }
 
 }  // namespace svmx

@@ -31,30 +31,64 @@ __device__ __forceinline__ float lane_xor1(float x) {
 // lanes 0-31 (and 32-63) hold 32 consecutive columns of one row.  Mirror: lanes r16 and r16 ^ 1
 // (xor 1) swap one of two neighbouring 16-row blocks, after which eight lanes hold 32
 // consecutive entries of one mirrored row as float4s.  The values stored are the same.
-template <bool STORE4>
-__device__ __forceinline__ void store_tile_128(float *__restrict__ G, int64_t ld, int64_t n, int64_t r0, int64_t c0,
-                                               int kq, int r16, const float (&kv)[4][4][4]) {
+typedef float tile_v4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// One value, four values.  NT: non-temporal, for 16-byte aligned rows (p a multiple of 4 floats
+// for four values).  Otherwise plain, at any alignment: 128-byte segments of unaligned rows
+// straddle lines, which L2 has to put together (non-temporal partial lines: 30,001 x 301 with
+// rows of 30,001 floats 2.3 ms against 1.7).
+template <bool NT>
+__device__ __forceinline__ void tile_put(float v, float *p) {
+  if (NT)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+template <bool NT>
+__device__ __forceinline__ void tile_put4(const float (&v)[4], float *p) {
+  if (NT)
+    __builtin_nontemporal_store((tile_v4f){v[0], v[1], v[2], v[3]}, reinterpret_cast<tile_v4f *>(p));
+  else
+    *reinterpret_cast<tile_v4u *>(p) = (tile_v4u){v[0], v[1], v[2], v[3]};
+}
+
+__device__ __forceinline__ float *tile_at(float *g, unsigned bytes) {
+  return reinterpret_cast<float *>(reinterpret_cast<char *>(g) + bytes);
+}
+
+template <bool NT, bool FULL>
+__device__ __forceinline__ void store_tile_128_as(float *__restrict__ G, int64_t ld, int64_t n, int64_t r0, int64_t c0,
+                                                  int kq, int r16, const float (&kv)[4][4][4]) {
   const bool odd = kq & 1;
+  // FULL: wave-uniform bases and one 32-bit lane offset, so a store costs no address arithmetic
+  const unsigned od = FULL ? 4u * (4u * (kq & 2) * (unsigned)ld + (odd ? 16u : 0u) + (unsigned)r16) : 0u;
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int jp = 0; jp < 2; ++jp)
+    for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
+      for (int jp = 0; jp < 2; ++jp) {
         const float A = kv[a][2 * jp][e], B = kv[a][2 * jp + 1][e];
         const float recv = lane_xor16(odd ? A : B);
-        const int64_t row1 = r0 + a * 16 + 4 * (kq & 2) + e, row2 = row1 + 4;
-        const int64_t col = c0 + (2 * jp + (odd ? 1 : 0)) * 16 + r16;
-        if (col < n) {
-          if (row1 < n) __builtin_nontemporal_store(odd ? recv : A, &G[row1 * ld + col]);
-          if (row2 < n) __builtin_nontemporal_store(odd ? B : recv, &G[row2 * ld + col]);
+        if (FULL) {
+          float *g = G + (r0 + a * 16 + e) * ld + c0 + 32 * jp;
+          tile_put<NT>(odd ? recv : A, tile_at(g, od));
+          tile_put<NT>(odd ? B : recv, tile_at(g + 4 * ld, od));
+        } else {
+          const int64_t row1 = r0 + a * 16 + 4 * (kq & 2) + e, row2 = row1 + 4;
+          const int64_t col = c0 + (2 * jp + (odd ? 1 : 0)) * 16 + r16;
+          if (col < n) {
+            if (row1 < n) tile_put<NT>(odd ? recv : A, &G[row1 * ld + col]);
+            if (row2 < n) tile_put<NT>(odd ? B : recv, &G[row2 * ld + col]);
+          }
         }
       }
   const bool odd1 = r16 & 1;
+  const unsigned om = FULL ? 4u * ((unsigned)(r16 & ~1) * (unsigned)ld + (odd1 ? 16u : 0u) + 4u * kq) : 0u;
 #pragma unroll
-  for (int ap = 0; ap < 2; ++ap)
+  for (int bb = 0; bb < 4; ++bb)
 #pragma unroll
-    for (int bb = 0; bb < 4; ++bb) {
+    for (int ap = 0; ap < 2; ++ap) {
       float v1[4], v2[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -63,23 +97,35 @@ __device__ __forceinline__ void store_tile_128(float *__restrict__ G, int64_t ld
         v1[e] = odd1 ? recv : P;
         v2[e] = odd1 ? Q : recv;
       }
-      const int64_t mr1 = c0 + bb * 16 + (r16 & ~1), mr2 = mr1 + 1;
-      const int64_t mc = r0 + 32 * ap + (odd1 ? 16 : 0) + 4 * kq;
+      if (FULL) {
+        float *g = G + (c0 + bb * 16) * ld + r0 + 32 * ap;
+        tile_put4<NT>(v1, tile_at(g, om));
+        tile_put4<NT>(v2, tile_at(g + ld, om));
+      } else {
+        const int64_t mr1 = c0 + bb * 16 + (r16 & ~1), mr2 = mr1 + 1;
+        const int64_t mc = r0 + 32 * ap + (odd1 ? 16 : 0) + 4 * kq;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int64_t mr = h ? mr2 : mr1;
-        const float *v = h ? v2 : v1;
-        if (mr >= n) continue;
-        float *dst = G + mr * ld + mc;
-        if (STORE4 && mc + 3 < n) {
-          __builtin_nontemporal_store((tile_v4f){v[0], v[1], v[2], v[3]}, reinterpret_cast<tile_v4f *>(dst));
-        } else {
+        for (int h = 0; h < 2; ++h) {
+          const int64_t mr = h ? mr2 : mr1;
+          const float(&v)[4] = h ? v2 : v1;
+          if (mr >= n) continue;
+          float *dst = G + mr * ld + mc;
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            if (mc + e < n) __builtin_nontemporal_store(v[e], &dst[e]);
+            if (mc + e < n) tile_put<NT>(v[e], &dst[e]);
         }
       }
     }
+}
+
+// r0 and c0 must be wave-uniform.
+template <bool NT>
+__device__ __forceinline__ void store_tile_128(float *__restrict__ G, int64_t ld, int64_t n, int64_t r0, int64_t c0,
+                                               int kq, int r16, const float (&kv)[4][4][4]) {
+  if (r0 + 64 <= n && c0 + 64 <= n && ld < (1 << 25))  // the lane offsets fit 32 bits
+    store_tile_128_as<NT, true>(G, ld, n, r0, c0, kq, r16, kv);
+  else
+    store_tile_128_as<NT, false>(G, ld, n, r0, c0, kq, r16, kv);
 }
 
 }  // namespace svmx

@@ -606,9 +606,9 @@ __device__ __forceinline__ void row_chunk_load(RowLoad &L, const SplitX &X, int6
                                                int lkq) {
 #pragma unroll
   for (int sl = 0; sl < 2; ++sl) {
-    const _Float16 *hb = sl ? X.lo : X.hi;
+    const int64_t off = 2 * k0 + 32 * sl;  // (k0 a multiple of 32)
     if (gb >= 0) {
-      const SVMX_GLOBAL h8 *q8 = gp(reinterpret_cast<const h8 *>(hb + gb * X.dp + k0)) + lkq;
+      const SVMX_GLOBAL h8 *q8 = gp(reinterpret_cast<const h8 *>(X.rows + gb * 2 * X.dp + off)) + lkq;
       L.r[2 * sl] = q8[0];
       L.r[2 * sl + 1] = q8[1];
     } else {
@@ -616,7 +616,7 @@ __device__ __forceinline__ void row_chunk_load(RowLoad &L, const SplitX &X, int6
       L.r[2 * sl + 1] = (h8){};
     }
     if (gs >= 0) {
-      const SVMX_GLOBAL h8 *q8 = gp(reinterpret_cast<const h8 *>(hb + gs * X.dp + k0)) + lkq;
+      const SVMX_GLOBAL h8 *q8 = gp(reinterpret_cast<const h8 *>(X.rows + gs * 2 * X.dp + off)) + lkq;
       L.r[4 + 2 * sl] = q8[0];
       L.r[4 + 2 * sl + 1] = q8[1];
     } else {
@@ -665,12 +665,12 @@ struct RowLoad64 {
 __device__ __forceinline__ void row64_load(RowLoad64 &L, const SplitX &X, const int64_t (&gb)[8],
                                            const int64_t (&gs)[8], int64_t k0, bool full) {
   const int c = threadIdx.x & 7, half = (threadIdx.x >> 3) & 1;
-  const _Float16 *hb = half ? X.lo : X.hi;
+  const int64_t off = 2 * k0 + (c >> 2) * 64 + half * 32 + (c & 3) * 8;
   const bool in = full || c < 4;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    L.b[i] = (gb[i] >= 0 && in) ? gp(reinterpret_cast<const h8 *>(hb + gb[i] * X.dp + k0))[c] : (h8){};
-    L.s[i] = (gs[i] >= 0 && in) ? gp(reinterpret_cast<const h8 *>(hb + gs[i] * X.dp + k0))[c] : (h8){};
+    L.b[i] = (gb[i] >= 0 && in) ? *gp(reinterpret_cast<const h8 *>(X.rows + gb[i] * 2 * X.dp + off)) : (h8){};
+    L.s[i] = (gs[i] >= 0 && in) ? *gp(reinterpret_cast<const h8 *>(X.rows + gs[i] * 2 * X.dp + off)) : (h8){};
   }
 }
 
