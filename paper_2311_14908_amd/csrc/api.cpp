@@ -495,11 +495,6 @@ svm_status class_sort(const int32_t *label, int64_t n, int32_t k, hipStream_t st
 // training samples each (n rows of X in all) and m test samples of d features, the compacted
 // support vectors, the partial sums, the problems' descriptions, and the split-fp16 rows of
 // both sets.
-struct PredictWs {
-  PredictScratch ps;
-  SplitX train, test;
-};
-
 constexpr int32_t PREDICT_PAIRS_MAX = 64;  // problems per prediction launch (bounds the partial sums)
 
 int64_t predict_scratch_bytes(int64_t n, int64_t ntr, int64_t pairs, int64_t m, int64_t d) {
@@ -514,32 +509,18 @@ int64_t predict_scratch_bytes(int64_t n, int64_t ntr, int64_t pairs, int64_t m, 
   return round_up(L.total, ALIGN);
 }
 
-PredictWs predict_scratch(void *base, int64_t n, int64_t ntr, int64_t pairs, int64_t m, int64_t d) {
+PredictScratch predict_scratch(void *base, int64_t n, int64_t ntr, int64_t pairs, int64_t m, int64_t d) {
   Layout L;
   char *b = static_cast<char *>(base);
-  PredictWs w;
-  w.ps.sv_row = reinterpret_cast<int32_t *>(b + L.add(4 * ntr * pairs));
-  w.ps.sv_coef = reinterpret_cast<double *>(b + L.add(8 * ntr * pairs));
-  w.ps.count = reinterpret_cast<int64_t *>(b + L.add(8 * pairs));
-  w.ps.part = reinterpret_cast<double *>(b + L.add(8LL * predict_splits(m, ntr) * std::max<int64_t>(m, 1) * pairs));
-  w.ps.pairs = reinterpret_cast<PredPair *>(b + L.add((int64_t)sizeof(PredPair) * pairs));
-  w.train = split_views(b + L.add(gram_split_scratch_bytes(n, d)), n, d);
-  w.test = split_views(b + L.add(gram_split_scratch_bytes(std::max<int64_t>(m, 1), d)), std::max<int64_t>(m, 1), d);
+  PredictScratch w;
+  w.sv_row = reinterpret_cast<int32_t *>(b + L.add(4 * ntr * pairs));
+  w.sv_coef = reinterpret_cast<double *>(b + L.add(8 * ntr * pairs));
+  w.count = reinterpret_cast<int64_t *>(b + L.add(8 * pairs));
+  w.part = reinterpret_cast<double *>(b + L.add(8LL * predict_splits(m, ntr) * std::max<int64_t>(m, 1) * pairs));
+  w.pairs = reinterpret_cast<PredPair *>(b + L.add((int64_t)sizeof(PredPair) * pairs));
+  w.split_train = split_views(b + L.add(gram_split_scratch_bytes(n, d)), n, d);
+  w.split_test = split_views(b + L.add(gram_split_scratch_bytes(std::max<int64_t>(m, 1), d)), std::max<int64_t>(m, 1), d);
   return w;
-}
-
-// Split rows of the training and test sets for the split-fp16 predict kernel (default), or
-// leave the fp32 kernel selected.
-hipError_t predict_prepare(PredictWs &w, const Opts &r, const float *Xtr, int64_t ntr, const float *T, int64_t m,
-                           int64_t d) {
-  if (r.gram_mfma != SVM_MFMA_SPLIT_F16) return hipSuccess;
-  hipError_t e = launch_split_rows(Xtr, ntr, d, w.train, r.stream);
-  if (e != hipSuccess) return e;
-  e = launch_split_rows(T, m, d, w.test, r.stream);
-  if (e != hipSuccess) return e;
-  w.ps.split_train = &w.train;
-  w.ps.split_test = &w.test;
-  return hipSuccess;
 }
 
 }  // namespace
@@ -916,8 +897,6 @@ svm_status svm_predict(const float *X_train, const int32_t *y, const double *alp
   if (need < 0) return fail(SVM_EINVAL, "sizes overflow 64-bit byte counts");
   if (!workspace || workspace_bytes < need)
     return fail(SVM_EWORKSPACE, "workspace of %lld bytes needed, %lld given", (long long)need, (long long)workspace_bytes);
-  PredictWs pw = predict_scratch(workspace, n, n, 1, m, d);
-  HIPCHK(predict_prepare(pw, r, X_train, n, X_test, m, d));
   PredPair pp{};
   pp.off0 = 0;
   pp.len0 = n;
@@ -930,8 +909,22 @@ svm_status svm_predict(const float *X_train, const int32_t *y, const double *alp
   pp.part_off = 0;
   pp.b = b;
   pp.nsplit = predict_splits(m, n);
-  HIPCHK(hipMemcpyAsync(pw.ps.pairs, &pp, sizeof(pp), hipMemcpyHostToDevice, r.stream));
-  HIPCHK(launch_predict_pairs(X_train, d, 1, pp.nsplit, alpha, gamma, X_test, m, dec, 1, pw.ps, r.stream));
+  PredictLaunch L{};
+  L.Xtr = X_train;
+  L.T = X_test;
+  L.n = n;
+  L.d = d;
+  L.m = m;
+  L.npairs = 1;
+  L.host_pairs = &pp;
+  L.alpha = alpha;
+  L.gamma = gamma;
+  L.split = r.gram_mfma == SVM_MFMA_SPLIT_F16;
+  L.split_test_rows = L.split_train_rows = L.split;
+  L.dec = dec;
+  L.dec_stride = 1;
+  L.ws = predict_scratch(workspace, n, n, 1, m, d);
+  HIPCHK(launch_predict_pairs(L, r.stream));
   HIPCHK(hipStreamSynchronize(r.stream));
   return SVM_OK;
 }
@@ -1188,8 +1181,18 @@ svm_status svm_predict_ovo(const float *X, const int32_t *label, int64_t n, int6
   if (m == 0) return SVM_OK;
   int32_t *dperm = static_cast<int32_t *>(workspace);
   const int32_t chunk = std::min<int32_t>(P, PREDICT_PAIRS_MAX);
-  PredictWs pw = predict_scratch(static_cast<char *>(workspace) + round_up(4 * n, ALIGN), n, n, chunk, m, d);
-  HIPCHK(predict_prepare(pw, r, X, n, X_test, m, d));
+  PredictLaunch L{};
+  L.Xtr = X;
+  L.T = X_test;
+  L.n = n;
+  L.d = d;
+  L.m = m;
+  L.perm = dperm;
+  L.alpha = alpha;
+  L.gamma = gamma;
+  L.split = r.gram_mfma == SVM_MFMA_SPLIT_F16;
+  L.dec_stride = P;
+  L.ws = predict_scratch(static_cast<char *>(workspace) + round_up(4 * n, ALIGN), n, n, chunk, m, d);
   HIPCHK(hipMemcpyAsync(dperm, perm.data(), 4 * n, hipMemcpyHostToDevice, r.stream));
   // the pairs in chunks of up to PREDICT_PAIRS_MAX, each chunk one launch per stage
   std::vector<PredPair> pp;
@@ -1212,17 +1215,22 @@ svm_status svm_predict_ovo(const float *X, const int32_t *label, int64_t n, int6
     }
   for (int32_t c0 = 0; c0 < P; c0 += chunk) {
     const int32_t np = std::min<int32_t>(chunk, P - c0);
-    int nsplit_max = 1;
     int64_t sv = 0, part = 0;
     for (int32_t q = c0; q < c0 + np; ++q) {
       pp[q].sv_off = sv;
       pp[q].part_off = part;
       sv += pp[q].ntr;
       part += (int64_t)pp[q].nsplit * m;
-      nsplit_max = std::max(nsplit_max, (int)pp[q].nsplit);
     }
-    HIPCHK(hipMemcpyAsync(pw.ps.pairs, pp.data() + c0, sizeof(PredPair) * np, hipMemcpyHostToDevice, r.stream));
-    HIPCHK(launch_predict_pairs(X, d, np, nsplit_max, alpha, gamma, X_test, m, dec + c0, P, pw.ps, r.stream));
+    HIPCHK(hipMemcpyAsync(L.ws.pairs, pp.data() + c0, sizeof(PredPair) * np, hipMemcpyHostToDevice, r.stream));
+    // the first chunk splits the rows: those that are a support vector of one of its problems if
+    // there is no other chunk, else all of them
+    L.split_test_rows = L.split_train_rows = L.split && c0 == 0;
+    L.all_train = np < P;
+    L.npairs = np;
+    L.host_pairs = pp.data() + c0;
+    L.dec = dec + c0;
+    HIPCHK(launch_predict_pairs(L, r.stream));
   }
   HIPCHK(launch_ovo_vote(dec, m, k, pred, r.stream));
   HIPCHK(hipStreamSynchronize(r.stream));

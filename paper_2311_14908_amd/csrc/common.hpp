@@ -51,18 +51,6 @@ hipError_t launch_solver(const SolveParams &p, int32_t total_wg, int32_t per_thr
 // error.
 int64_t solver_res_rows_max(const SolveParams &p, int32_t per_thread);
 hipError_t launch_finalize(const Prob *probs, int32_t nprob, double C, double *out /*[nprob][4]*/, hipStream_t s);
-// Device scratch of a prediction: compacted support vectors and per-split partial sums of
-// every problem of one launch, and the problems' descriptions.
-struct PredictScratch {
-  int32_t *sv_row;  // [sum of the problems' ntr]
-  double *sv_coef;  // [sum of the problems' ntr]
-  int64_t *count;   // [problems]
-  double *part;     // [sum of the problems' nsplit][m]
-  struct PredPair *pairs;  // [problems], device
-  const SplitX *split_train = nullptr;  // split rows of the training X and of the test samples
-  const SplitX *split_test = nullptr;   // (both set: the split-fp16 kernel; host pointers)
-};
-int predict_splits(int64_t m, int64_t nsv_max);
 // One problem of a prediction launch: its training samples addressed like Prob (local j -> row
 // off0+j or off1+j-len0, then through perm when perm != NULL; labels from y by that row, or by
 // range), its multipliers alpha[alpha_off ..][ntr], where its support vectors and partial sums
@@ -75,12 +63,37 @@ struct PredPair {
   double b;
   int32_t nsplit, pad;
 };
-// Decision values of npairs problems in one launch per stage: dec[q * dec_stride + p] for test
-// sample q and problem p (pairs[] already on the device, in ws.pairs); nsplit_max = the
-// largest nsplit among them.
-hipError_t launch_predict_pairs(const float *Xtr, int64_t d, int32_t npairs, int nsplit_max, const double *alpha,
-                                double gamma, const float *T, int64_t m, double *dec, int64_t dec_stride,
-                                const PredictScratch &ws, hipStream_t s);
+int predict_splits(int64_t m, int64_t nsv_max);
+// Device scratch of a prediction: compacted support vectors and per-split partial sums of
+// every problem of one launch, the problems' descriptions, and the split rows of the training X
+// and of the test samples.
+struct PredictScratch {
+  int32_t *sv_row;  // [sum of the problems' ntr]
+  double *sv_coef;  // [sum of the problems' ntr]
+  int64_t *count;   // [problems]
+  double *part;     // [sum of the problems' nsplit][m]
+  PredPair *pairs;  // [problems], device
+  SplitX split_train, split_test;
+};
+// Decision values of npairs (at most 64) problems in one launch per stage: dec[q * dec_stride + p]
+// for test sample q and problem p.  host_pairs: the problems; with more than one they must also
+// be on the device already, in ws.pairs.  split: the split-fp16 kernel; split_test_rows and
+// split_train_rows say which rows this launch splits first (n training positions, through perm;
+// all_train: all of them, else only support vectors of these problems).
+struct PredictLaunch {
+  const float *Xtr, *T;
+  int64_t n, d, m;
+  int32_t npairs;
+  const PredPair *host_pairs;
+  const int32_t *perm;
+  const double *alpha;
+  double gamma;
+  bool split, split_test_rows, split_train_rows, all_train;
+  double *dec;
+  int64_t dec_stride;
+  PredictScratch ws;
+};
+hipError_t launch_predict_pairs(const PredictLaunch &L, hipStream_t s);
 hipError_t launch_ovo_vote(const double *dec, int64_t m, int32_t k, int32_t *pred, hipStream_t s);
 
 // Working-set solver (ws_smo.hip): one problem per launch, nwg sample-owning workgroups plus,

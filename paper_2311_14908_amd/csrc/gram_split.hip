@@ -10,6 +10,7 @@
 // fp32 product on the 157 TFLOP/s path; measured against the fp64 difference form, the values
 // are as accurate as those of the fp32 MFMA kernel.  The row norms are fp64 sums of the fp32
 // inputs.
+#include "split_rows.hpp"
 #include "split_tile.hpp"
 #include "tile_order.hpp"
 #include "tile_store.hpp"
@@ -37,95 +38,8 @@ SplitX split_views(void *scratch, int64_t n, int64_t d) {
   return s;
 }
 
-// s = 2^e with max|x| < 2^e, h = fp16(x / s), l = fp16(x / s - h), and the norm |x|^2 as an fp64
-// sum rounded to fp32.  gs lanes a row (a power of two covering its chunks of 8 features, at most
-// 64): each lane reads 8 consecutive features at once (two 16-byte loads, whatever the alignment
-// of the row) and writes 16 bytes of each half, so every store instruction of a wave fills whole
-// 128-byte lines.  Up to SPLIT_KEEP chunks a lane stay in registers between the two passes.
-// Bound by reading X and writing as many bytes: 20,000 x 784 20 us, against 34 us with one
-// feature a lane (2-byte stores).
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-constexpr int SPLIT_KEEP = 4;
-
-__device__ __forceinline__ void split_chunk_load(const float *__restrict__ x, int64_t d, int64_t k, float (&v)[8]) {
-  if (k + 8 <= d) {
-    const f4u a = *reinterpret_cast<const f4u *>(x + k), b = *reinterpret_cast<const f4u *>(x + k + 4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[e] = a[e];
-      v[4 + e] = b[e];
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = k + e < d ? x[k + e] : 0.f;
-  }
-}
-
-__device__ __forceinline__ void split_chunk_store(_Float16 *__restrict__ row, int64_t k, float inv, const float (&v)[8]) {
-  h8 h, l;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float w = v[e] * inv;  // exact (power of two)
-    h[e] = (_Float16)w;
-    l[e] = (_Float16)(w - (float)h[e]);  // w - h is exact in fp32
-  }
-  _Float16 *p = row + (k >> 5) * 64 + (k & 31);
-  *reinterpret_cast<h8 *>(p) = h;
-  *reinterpret_cast<h8 *>(p + 32) = l;
-}
-
-__global__ void __launch_bounds__(256) gram_split_k(const float *__restrict__ X, int64_t n, int64_t d, SplitX s, int gs) {
-  const int g = threadIdx.x & (gs - 1);
-  const int64_t chunks = s.dp >> 3;
-  const int64_t groups = (int64_t)gridDim.x * (256 / gs);
-  // every lane of a wave runs the same number of rounds (the reductions cross lanes)
-  for (int64_t r0 = (int64_t)blockIdx.x * (256 / gs); r0 < n; r0 += groups) {
-    const int64_t r = r0 + threadIdx.x / gs;
-    const bool in = r < n;
-    const float *x = X + (in ? r : 0) * d;
-    float v[SPLIT_KEEP][8];
-    float m = 0.f;
-    double q = 0.0;
-    auto take = [&](const float (&c)[8]) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        m = fmaxf(m, fabsf(c[e]));
-        q = __builtin_fma((double)c[e], (double)c[e], q);
-      }
-    };
-#pragma unroll
-    for (int i = 0; i < SPLIT_KEEP; ++i)
-      if (g + i * gs < chunks) split_chunk_load(x, d, 8 * (int64_t)(g + i * gs), v[i]);
-#pragma unroll
-    for (int i = 0; i < SPLIT_KEEP; ++i)
-      if (g + i * gs < chunks) take(v[i]);
-    for (int64_t c = g + (int64_t)SPLIT_KEEP * gs; c < chunks; c += gs) {
-      float w[8];
-      split_chunk_load(x, d, 8 * c, w);
-      take(w);
-    }
-    for (int o = gs >> 1; o > 0; o >>= 1) {
-      m = fmaxf(m, __shfl_xor(m, o));
-      q += __shfl_xor(q, o);
-    }
-    if (!in) continue;
-    int e = 0;
-    if (m > 0.f) (void)frexpf(m, &e);  // m = f 2^e, f in [0.5, 1)
-    const float inv = ldexpf(1.0f, -e);
-    _Float16 *row = s.rows + r * 2 * s.dp;
-#pragma unroll
-    for (int i = 0; i < SPLIT_KEEP; ++i)
-      if (g + i * gs < chunks) split_chunk_store(row, 8 * (int64_t)(g + i * gs), inv, v[i]);
-    for (int64_t c = g + (int64_t)SPLIT_KEEP * gs; c < chunks; c += gs) {
-      float w[8];
-      split_chunk_load(x, d, 8 * c, w);
-      split_chunk_store(row, 8 * c, inv, w);
-    }
-    if (g == 0) {
-      s.scale[r] = ldexpf(1.0f, e);
-      s.nrm[r] = (float)q;
-    }
-  }
+__global__ void __launch_bounds__(256) gram_split_k(SplitRows p, int64_t d) {
+  split_rows_block(p, d, blockIdx.x, gridDim.x, [](int64_t pos) { return pos; });
 }
 
 // One 128x128 tile of the upper triangle per workgroup; workgroup b runs on XCD b % 8 and takes
@@ -171,7 +85,8 @@ __global__ void __launch_bounds__(SBS, 4) gram_rbf_f16x3(SplitX s, int64_t n, fl
   for (int q = 0; q < SCH; ++q)
     src[q] = split_src(s, min<int64_t>((w < 2 ? i0 : j0) + ((w & 1) * SCH + q) * 8 + (lane >> 3), n - 1));
   v4f acc[4][4];
-  split_tile(S, src, s.dp / SKS, wm, wn, acc);
+  split_stage_load(S, src);
+  split_tile_loaded(S, src, s.dp / SKS, wm, wn, acc);
   const bool diag = i0 == j0;
   float kv[4][4][4];
 #pragma unroll
@@ -201,12 +116,8 @@ __global__ void __launch_bounds__(SBS, 4) gram_rbf_f16x3(SplitX s, int64_t n, fl
 
 hipError_t launch_split_rows(const float *X, int64_t n, int64_t d, const SplitX &s, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  int gs = 1;  // lanes a row
-  while (gs < 64 && (int64_t)gs * 8 < s.dp) gs <<= 1;
-  const int64_t per = 256 / gs;
-  int64_t pb = (n + per - 1) / per;
-  if (pb > 8192) pb = 8192;
-  hipLaunchKernelGGL(gram_split_k, dim3((unsigned)pb), dim3(256), 0, st, X, n, d, s, gs);
+  const SplitRows p = split_rows_of(X, n, s);
+  hipLaunchKernelGGL(gram_split_k, dim3((unsigned)split_rows_blocks(p)), dim3(256), 0, st, p, d);
   return hipGetLastError();
 }
 

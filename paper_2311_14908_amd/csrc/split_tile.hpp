@@ -72,19 +72,21 @@ __device__ __forceinline__ void split_stage_mma(const SplitStage &S, int wm, int
   }
 }
 
-// The whole contraction of a tile: one LDS stage (32 KB), loaded, then multiplied; the other
-// workgroups of the CU multiply meanwhile.  Ends with every operand read but without a barrier.
-__device__ __forceinline__ void split_tile(SplitStage &S, const char *(&src)[SCH], int64_t stages, int wm, int wn,
-                                           v4f (&acc)[4][4]) {
+// The contraction of a tile whose first stage is already on its way: one LDS stage (32 KB),
+// loaded, then multiplied; the other workgroups of the CU multiply meanwhile.  Ends with a barrier
+// after the last operand has been read.
+__device__ __forceinline__ void split_tile_loaded(SplitStage &S, const char *(&src)[SCH], int64_t stages, int wm, int wn,
+                                                  v4f (&acc)[4][4]) {
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[a][b] = (v4f){0.f, 0.f, 0.f, 0.f};
-  for (int64_t st = 0; st < stages; ++st) {
-    if (st > 0) __syncthreads();  // the previous stage's operands have been read
-    split_stage_load(S, src);
-    __syncthreads();              // waits for the loads, too
+  for (int64_t st = 1;; ++st) {
+    __syncthreads();  // waits for the loads, too
     split_stage_mma(S, wm, wn, acc);
+    __syncthreads();  // this stage's operands have been read
+    if (st >= stages) break;
+    split_stage_load(S, src);
   }
 }
 

@@ -54,3 +54,55 @@ def test_gram_store_kinds(ld):
     ref[torch.arange(len(rows)), rows] = 1.0
     assert float(((G[rows, :n].double() - ref).abs() / ref).max()) <= REL
     assert torch.equal(G[:, rows], G[rows, :n].T.contiguous())
+
+
+def _decision64(X, y, alpha, b, gamma, T):
+    sv = alpha.nonzero()[:, 0]
+    A, B = T.double(), X[sv].double()
+    d2 = A.square().sum(1)[:, None] + B.square().sum(1)[None, :] - 2.0 * A @ B.T
+    coef = alpha[sv] * y[sv].double()
+    # each kernel value is good to about 1e-6 (see REL): the sum to that share of sum |coef|
+    return torch.exp(-gamma * d2.clamp_(min=0.0)) @ coef - b, 2e-6 * float(coef.abs().sum()) + 1e-12
+
+
+@pytest.mark.parametrize("mfma", [svmx.MFMA_SPLIT_F16, svmx.MFMA_F32])
+@pytest.mark.parametrize("n,nsv,m,d", [
+    (1, 0, 1, 3), (5, 1, 1, 1), (128, 128, 128, 32), (129, 129, 127, 33), (1023, 127, 129, 40), (1024, 256, 1, 64),
+    (1025, 1025, 257, 17), (2049, 300, 1100, 96), (70001, 40000, 130, 8), (70001, 3, 5, 8), (9000, 8999, 2, 2100)])
+def test_predict_edges(n, nsv, m, d, mfma):
+    """No, one and a ragged last tile of support vectors; compaction chunks of 1,024 samples and more,
+    empty ones among them; one and many splits; the last chunk's support vectors at the end."""
+    X, T = _x(n, d, n + d), _x(m, d, m)
+    rng = np.random.default_rng(nsv)
+    y = torch.from_numpy(np.where(rng.random(n) < 0.5, 1, -1).astype(np.int32)).cuda()
+    a = np.zeros(n)
+    at = rng.choice(n, nsv, replace=False)
+    if 0 < nsv:
+        at[0] = n - 1 if n - 1 not in at else at[0]
+    a[at] = rng.random(nsv) + 0.1
+    alpha = torch.from_numpy(a).cuda()
+    dec = svmx.svm_predict(X, y, alpha, 0.25, 4.0 / d, T, gram_mfma=mfma)
+    ref, tol = _decision64(X, y, alpha, 0.25, 4.0 / d, T)
+    assert float((dec - ref).abs().max()) <= tol
+    again = svmx.svm_predict(X, y, alpha, 0.25, 4.0 / d, T, gram_mfma=mfma)
+    assert torch.equal(dec, again)
+
+
+@pytest.mark.parametrize("k,per,m", [(2, 40, 3), (3, 5, 130), (12, 30, 70), (64, 3, 9)])
+def test_ovo_votes_are_those_of_its_decisions(k, per, m):
+    """Ties and every vote count: the classes follow from the returned decision values."""
+    d, n = 6, k * per
+    X, T = _x(n, d, k), _x(m, d, k + 1)
+    lab = torch.from_numpy(np.random.default_rng(k).permutation(np.arange(n) % k).astype(np.int32)).cuda()
+    pairs = k * (k - 1) // 2
+    a = torch.rand((k - 1) * n, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(k))
+    a[a < 0.5] = 0.0
+    dec, pred = svmx.svm_predict_ovo(X, lab, k, a, np.zeros(pairs), 1.0, T)
+    dec = dec.cpu().numpy()
+    votes, p = np.zeros((m, k), dtype=int), 0
+    for i in range(k):
+        for j in range(i + 1, k):
+            votes[:, i] += dec[:, p] > 0
+            votes[:, j] += dec[:, p] <= 0
+            p += 1
+    assert np.array_equal(pred.cpu().numpy(), votes.argmax(1))
