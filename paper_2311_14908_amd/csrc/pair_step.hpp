@@ -132,6 +132,90 @@ __device__ __forceinline__ int winner_lane(double v, int i) {
   return tie_lane(v == rv, i);
 }
 
+// Total order of (value, index) on 32-bit words, for reductions whose every round is one
+// v_min_u32 with a DPP operand: the words of an ascending key of a double (negate for a maximum;
+// -0 must not occur, it would order below +0).
+__device__ __forceinline__ void order_words(double v, unsigned &hi, unsigned &lo) {
+  const long long b = __double_as_longlong(v);
+  const int s = (int)(b >> 63);
+  hi = (unsigned)(b >> 32) ^ ((unsigned)s | 0x80000000u);
+  lo = (unsigned)b ^ (unsigned)s;
+}
+
+template <int CTRL>
+__device__ __forceinline__ unsigned dpp_min_u32(unsigned v) {  // every lane reads its source lane
+  const unsigned o = (unsigned)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, false);
+  return o < v ? o : v;
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ unsigned dpp_min_u32_rows(unsigned v) {
+  const unsigned o = (unsigned)dpp_mov<CTRL, ROW_MASK>((int)v);
+  return o < v ? o : v;
+}
+
+// Minimum over groups of N lanes (N = 4, 8, 16: DPP inside rows, to every lane of the group; 64:
+// to every lane of the wave, in a scalar register).
+template <int N>
+__device__ __forceinline__ void lanes_min2(unsigned &a, unsigned &b) {
+  a = dpp_min_u32<0xB1>(a);  // quad_perm [1,0,3,2]
+  b = dpp_min_u32<0xB1>(b);
+  a = dpp_min_u32<0x4E>(a);  // quad_perm [2,3,0,1]
+  b = dpp_min_u32<0x4E>(b);
+  if (N >= 8) {
+    a = dpp_min_u32<0x124>(a);  // row_ror:4
+    b = dpp_min_u32<0x124>(b);
+  }
+  if (N >= 16) {
+    a = dpp_min_u32<0x128>(a);  // row_ror:8
+    b = dpp_min_u32<0x128>(b);
+  }
+  if (N == 64) {
+    a = dpp_min_u32_rows<0x142, 0xA>(a);  // row_bcast:15 -> rows 1, 3
+    b = dpp_min_u32_rows<0x142, 0xA>(b);
+    a = dpp_min_u32_rows<0x143, 0xC>(a);  // row_bcast:31 -> rows 2, 3
+    b = dpp_min_u32_rows<0x143, 0xC>(b);
+    a = (unsigned)__builtin_amdgcn_readlane((int)a, 63);
+    b = (unsigned)__builtin_amdgcn_readlane((int)b, 63);
+  }
+}
+
+// The first of the N lowest lanes that holds the smallest (hi, lo, i), given those with the
+// smallest hi: lo and i are only looked at when several lanes share the smallest hi (the 20
+// leading mantissa bits).
+template <int N>
+__device__ __forceinline__ int first_of(unsigned long long m, unsigned lo, unsigned i) {
+  if (N < 64) m &= (1ull << (N & 63)) - 1ull;
+  if (__builtin_expect((m & (m - 1)) == 0, 1)) return __builtin_ctzll(m);
+  const int lane = threadIdx.x & 63;
+  unsigned a = (m >> lane) & 1 ? lo : 0xffffffffu, b = a;
+  lanes_min2<64>(a, b);
+  m &= (unsigned long long)__ballot(lo == a);
+  if ((m & (m - 1)) == 0) return __builtin_ctzll(m);
+  a = b = (m >> lane) & 1 ? i : 0xffffffffu;
+  lanes_min2<64>(a, b);
+  return __builtin_ctzll(m & (unsigned long long)__ballot(i == a));
+}
+
+// Lanes of the two winners among the N lowest lanes (N < 64: lanes q, q + N, ... hold the same):
+// smallest (vu, iu) and largest (vl, smallest il).  Called by all 64 lanes; uniform results.
+template <int N>
+__device__ __forceinline__ void winner_lanes(double vu, unsigned iu, double vl, unsigned il, int &lu, int &ll) {
+  unsigned hu, ou, hl, ol;
+  order_words(vu, hu, ou);
+  order_words(-vl, hl, ol);
+  unsigned mu = hu, ml = hl;
+  lanes_min2<N>(mu, ml);
+  lu = first_of<N>((unsigned long long)__ballot(hu == mu), ou, iu);
+  ll = first_of<N>((unsigned long long)__ballot(hl == ml), ol, il);
+}
+
+__device__ __forceinline__ double uniform_d(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(b >> 32));
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)b);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 __device__ __forceinline__ void st_word(u64 *p, u64 v) {
   __hip_atomic_store(gp(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

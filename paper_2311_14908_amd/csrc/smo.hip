@@ -62,26 +62,6 @@ __device__ __forceinline__ void sel_merge(Sel &s, const Sel &o) {
   if (gt_max(o.vl, o.il, s.vl, s.il)) { s.vl = o.vl; s.il = o.il; s.al = o.al; s.yl = o.yl; }
 }
 
-// Wave-wide selection, returned to every lane.  Must be called by all 64 lanes of the wave.
-// Each side's winner: its extreme value, then the smallest index among the lanes holding it
-// (the (value, index) lexicographic order; -0 and +0 compare equal), with value, index,
-// multiplier and label read from that lane.  The two sides' reductions run interleaved.
-__device__ __forceinline__ Sel sel_wave(const Sel &mine) {
-  double ru = mine.vu, rl = mine.vl;
-  wave_minmax(ru, rl);
-  const int lu = tie_lane(mine.vu == ru, mine.iu), ll = tie_lane(mine.vl == rl, mine.il);
-  Sel r;
-  r.vu = readlane_d(mine.vu, lu);  // the winner's own value (its sign of zero included)
-  r.iu = __builtin_amdgcn_readlane(mine.iu, lu);
-  r.au = readlane_d(mine.au, lu);
-  r.yu = __builtin_amdgcn_readlane(mine.yu, lu);
-  r.vl = readlane_d(mine.vl, ll);
-  r.il = __builtin_amdgcn_readlane(mine.il, ll);
-  r.al = readlane_d(mine.al, ll);
-  r.yl = __builtin_amdgcn_readlane(mine.yl, ll);
-  return r;
-}
-
 // Candidate of the second-order choice of l (used with p.second_order): the largest gain
 // g = (f_t - b_up)^2 / a_ut over the members t of I_low above b_up (ties to the smaller index),
 // with f, multiplier, label and K(u, t) of that sample.
@@ -90,15 +70,12 @@ struct Sel2 {
   int il, yl;
 };
 
-__device__ __forceinline__ void rec_init(Sel &s) { sel_init(s); }
 __device__ __forceinline__ void rec_init(Sel2 &s) {
   s.g = -INFINITY; s.fl = 0.0; s.al = 0.0; s.kul = 0.0; s.il = IBIG; s.yl = 0;
 }
-__device__ __forceinline__ void rec_merge(Sel &s, const Sel &o) { sel_merge(s, o); }
 __device__ __forceinline__ void rec_merge(Sel2 &s, const Sel2 &o) {
   if (gt_max(o.g, o.il, s.g, s.il)) s = o;
 }
-__device__ __forceinline__ Sel rec_wave(const Sel &mine) { return sel_wave(mine); }
 __device__ __forceinline__ Sel2 rec_wave(const Sel2 &mine) {
   const int lane = winner_lane<true>(mine.g, mine.il);
   Sel2 r;
@@ -109,6 +86,12 @@ __device__ __forceinline__ Sel2 rec_wave(const Sel2 &mine) {
   r.il = __builtin_amdgcn_readlane(mine.il, lane);
   r.yl = __builtin_amdgcn_readlane(mine.yl, lane);
   return r;
+}
+
+__device__ __forceinline__ unsigned pack_index(int i, int y) { return (unsigned)i | (y < 0 ? 0x80000000u : 0u); }
+__device__ __forceinline__ void unpack_index(unsigned w, int &i, int &y) {
+  i = (int)(w & 0x7fffffffu);
+  y = (w >> 31) ? -1 : 1;
 }
 
 // LDS hand-off between the waves of a workgroup.  Two buffers used alternately, so one
@@ -130,14 +113,46 @@ __device__ __forceinline__ R rec_block(const R &wave_res, RecLds<R, NW> &L, int 
   return r;
 }
 
-__device__ __forceinline__ unsigned pack_index(int i, int y) { return (unsigned)i | (y < 0 ? 0x80000000u : 0u); }
-__device__ __forceinline__ void unpack_index(unsigned w, int &i, int &y) {
-  i = (int)(w & 0x7fffffffu);
-  y = (w >> 31) ? -1 : 1;
+// The same hand-off for the two candidates of the first-order rule.  A wave's two winning lanes
+// write their own fields; after the barrier lane q of every wave reads wave q's candidates, the
+// winners are found among those lanes, and their fields come out in scalar registers, so that
+// the addresses, tests and the pair's multipliers that follow are scalar.
+// The step of a problem is a chain of such short stages and bound by their latency, instruction
+// after instruction of one wave a SIMD: reducing 32-bit leading words (a move and a v_min_u32 a
+// round) instead of (value, index) pairs of doubles, letting lanes combine the waves instead of
+// every thread in turn, branch-free offers, scalar addresses and tests, and issuing the rows'
+// loads before the tests took a step from 4.08 to 3.29 us at 20,000 x 784 (40 workgroups; 2.0 us
+// of it the exchange) and from 2.1 to 1.5 us at 1,000 x 16 (one workgroup), from 4.61 to 3.72 us at
+// 50,000 x 128 and from 5.23 to 4.01 at 100,000 x 32, bit for bit the same.
+struct SelRec {
+  double vu, au, vl, al;
+  unsigned wu, wl;  // index | label
+};
+
+template <int NW>
+struct SelLds {
+  SelRec slot[2][NW];
+};
+
+// The lane of each winner writes it.
+__device__ __forceinline__ void sel_put(SelRec &r, const Sel &s, int lu, int ll) {
+  const int lane = threadIdx.x & 63;
+  if (lane == lu) { r.vu = s.vu; r.au = s.au; r.wu = pack_index(s.iu, s.yu); }
+  if (lane == ll) { r.vl = s.vl; r.al = s.al; r.wl = pack_index(s.il, s.yl); }
 }
 
-// Limbs of a record (xchg_record.hpp): v_up, a_up, index words, v_low, a_low; the label travels
-// in bit 31 of the index word.
+// The winners of lanes 0 .. N-1, each a candidate of its own, in scalar registers.
+__device__ __forceinline__ Sel sel_from_lanes(const SelRec &r, int lu, int ll) {
+  Sel s;
+  s.vu = readlane_d(r.vu, lu);
+  s.au = readlane_d(r.au, lu);
+  unpack_index((unsigned)__builtin_amdgcn_readlane((int)r.wu, lu), s.iu, s.yu);
+  s.vl = readlane_d(r.vl, ll);
+  s.al = readlane_d(r.al, ll);
+  unpack_index((unsigned)__builtin_amdgcn_readlane((int)r.wl, ll), s.il, s.yl);
+  return s;
+}
+
 __device__ __forceinline__ void rec_limbs_of(const Sel &s, u64 (&L)[5]) {
   L[0] = (u64)__double_as_longlong(s.vu);
   L[1] = (u64)__double_as_longlong(s.au);
@@ -145,6 +160,32 @@ __device__ __forceinline__ void rec_limbs_of(const Sel &s, u64 (&L)[5]) {
   L[3] = (u64)__double_as_longlong(s.vl);
   L[4] = (u64)__double_as_longlong(s.al);
 }
+// A record of scalar fields: the six words are packed by the scalar unit and dealt to lanes 0-5.
+__device__ __forceinline__ void put_record_uniform(u64 *rec, unsigned stamp, const Sel &s) {
+  u64 L[5];
+  rec_limbs_of(s, L);
+  const int t = threadIdx.x & 63;
+  u64 mine = rec_word(L, 0, stamp);
+#pragma unroll
+  for (int w = 1; w < REC_WORDS; ++w) {
+    const u64 v = rec_word(L, w, stamp);
+    mine = t == w ? v : mine;
+  }
+  if (t < REC_WORDS) st_word(rec + t, mine);
+}
+
+// slots: one record per wave, written before the call; ends with the workgroup's winners.
+template <int NW>
+__device__ __forceinline__ Sel sel_combine(const SelRec (&slot)[NW]) {
+  __syncthreads();
+  const SelRec r = slot[threadIdx.x & (NW - 1)];
+  int lu, ll;
+  winner_lanes<NW>(r.vu, r.wu & 0x7fffffffu, r.vl, r.wl & 0x7fffffffu, lu, ll);
+  return sel_from_lanes(r, lu, ll);
+}
+
+// Limbs of a record (xchg_record.hpp): v_up, a_up, index words, v_low, a_low; the label travels
+// in bit 31 of the index word.
 __device__ __forceinline__ void rec_from_limbs(const u64 (&L)[5], Sel &o) {
   o.vu = __longlong_as_double((long long)L[0]);
   o.au = __longlong_as_double((long long)L[1]);
@@ -254,6 +295,107 @@ __device__ R exchange(const Prob &P, int rank, unsigned stamp, const R &mine, Re
   return r;
 }
 
+// exchange for the first-order candidates: the same protocol; the lanes that hold the winning
+// records write them to LDS, and every wave reads the one result into scalar registers.
+__device__ __forceinline__ void poll_lanes(const u64 *words, int q0, int q1, int stride, unsigned stamp,
+                                           uint64_t spin_limit, int32_t *err, int *abort_flag, Sel &s, int &lu, int &ll) {
+  sel_init(s);
+  for (int q = q0 + (int)(threadIdx.x & 63); q < q1; q += stride) {
+    const u64 *rec = words + (size_t)q * SLOT_WORDS;
+    u64 w[REC_WORDS];
+    const uint64_t t0 = wall_clock64();
+    for (;;) {
+      bool ok = true;
+#pragma unroll
+      for (int k = 0; k < REC_WORDS; ++k) {
+        w[k] = ld_word(rec + k);
+        ok = ok && rec_stamped(w[k], stamp);
+      }
+      if (ok) break;
+      if (wall_clock64() - t0 > spin_limit) {
+        __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *abort_flag = 1;
+        break;
+      }
+    }
+    u64 L[5];
+    rec_limbs(w, L);
+    Sel o;
+    rec_from_limbs(L, o);
+    if (q < q0 + 64)
+      s = o;
+    else
+      sel_merge(s, o);
+  }
+  winner_lanes<64>(s.vu, (unsigned)s.iu, s.vl, (unsigned)s.il, lu, ll);
+}
+
+// What the exchange needs of a problem and of the workgroup's place in it.
+struct Xchg {
+  u64 *slots, *slots2;
+  int nwg, g1, ng, rank, group, q0, q1;  // q0 .. q1: the group whose leader this workgroup is (else empty)
+};
+
+__device__ __forceinline__ Xchg xchg_of(const Prob &P, int rank) {
+  Xchg x;
+  x.slots = P.slots;
+  x.slots2 = P.slots2;
+  x.nwg = P.nwg;
+  x.g1 = P.g1;
+  x.ng = P.ng;
+  x.rank = rank;
+  x.group = P.g1 > 0 ? __builtin_amdgcn_readfirstlane(rank / P.g1) : 0;
+  const bool leads = P.g1 > 0 && rank == group_leader(P, x.group);
+  x.q0 = x.group * P.g1;
+  x.q1 = leads ? min(P.nwg, x.q0 + P.g1) : x.q0;
+  return x;
+}
+
+template <int NW>
+__device__ __forceinline__ Sel sel_exchange(const Xchg &x, unsigned stamp, const Sel &mine, SelLds<NW> &L, int &buf,
+                                            uint64_t spin_limit, int32_t *err, int *abort_flag, bool &aborted) {
+  const unsigned par = stamp & 1u;
+  u64 *lv1 = x.slots + par * (unsigned)x.nwg * SLOT_WORDS;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wave == 0) put_record_uniform(lv1 + x.rank * SLOT_WORDS, stamp, mine);
+  int pollers = 1, lu, ll;
+  Sel s;
+  if (x.g1 > 0) {
+    if (wave == 0) {
+      u64 *lv2 = x.slots2 + par * (unsigned)x.ng * SLOT_WORDS;
+      if (x.q1 > x.q0) {
+        poll_lanes(lv1, x.q0, x.q1, 64, stamp, spin_limit, err, abort_flag, s, lu, ll);
+        SelRec r{s.vu, s.au, s.vl, s.al, pack_index(s.iu, s.yu), pack_index(s.il, s.yl)};
+        put_record_uniform(lv2 + x.group * SLOT_WORDS, stamp, sel_from_lanes(r, lu, ll));
+      }
+      poll_lanes(lv2, 0, x.ng, 64, stamp, spin_limit, err, abort_flag, s, lu, ll);
+      sel_put(L.slot[buf][0], s, lu, ll);
+    }
+  } else {
+    pollers = min(NW, (x.nwg + 63) >> 6);
+    if (wave < pollers) {
+      poll_lanes(lv1, wave * 64, x.nwg, 64 * pollers, stamp, spin_limit, err, abort_flag, s, lu, ll);
+      sel_put(L.slot[buf][wave], s, lu, ll);
+    } else if (pollers > 1) {  // an empty candidate, for the combination
+      sel_init(s);
+      sel_put(L.slot[buf][wave], s, 0, 0);
+    }
+  }
+  Sel r;
+  if (__builtin_expect(pollers > 1, 0)) {
+    r = sel_combine<NW>(L.slot[buf]);
+    aborted = *abort_flag != 0;
+  } else {
+    __syncthreads();
+    const SelRec rec = L.slot[buf][0];
+    const int ab = *abort_flag;
+    r = sel_from_lanes(rec, 0, 0);
+    aborted = __builtin_amdgcn_readfirstlane(ab) != 0;
+  }
+  buf ^= 1;
+  return r;
+}
+
 __device__ __forceinline__ int64_t gmap(const Prob &P, int64_t j) { return j < P.len0 ? P.off0 + j : P.off1 + (j - P.len0); }
 __device__ __forceinline__ int label_of(const Prob &P, int64_t j) {
   return P.y ? gp(P.y)[gmap(P, j)] : (j < P.len0 ? 1 : -1);
@@ -270,13 +412,89 @@ __device__ __forceinline__ double so_gain(double ft, double bup, float kut) {
   return bt * bt / at;
 }
 
-// Offer sample j (value f, multiplier a, label y) to this thread's candidates.
-__device__ __forceinline__ void consider(Sel &s, double f, double a, int y, int j, double C) {
-  const bool up = (y > 0 && a < C) || (y < 0 && a > 0.0);
-  const bool lo = (y > 0 && a > 0.0) || (y < 0 && a < C);
-  if (up && lt_min(f, j, s.vu, s.iu)) { s.vu = f; s.iu = j; s.au = a; s.yu = y; }
-  if (lo && gt_max(f, j, s.vl, s.il)) { s.vl = f; s.il = j; s.al = a; s.yl = y; }
-}
+// This thread's samples and their candidates.  Membership of I_up and I_low is kept per sample and
+// only changes for u and l.  Gram path: as what is added to its f before it is compared, 0 for a
+// member (which also turns -0 into +0), +-infinity otherwise, so offering a sample costs an
+// addition, a compare and three selects a side and no branch.  Row path (FLAGS): as bits, for its
+// registers are needed by the rows.
+template <int BS, int PER, bool FLAGS>
+struct Own {
+  static constexpr int NP = FLAGS ? 1 : PER;
+  double f[PER], a[PER], pu[NP], pl[NP];
+  unsigned mu, ml;  // FLAGS: bit k: sample k is in I_up, in I_low
+  unsigned ypos;    // bit k: the label of sample k is +1
+  double bu, bl;    // best value of each side, and which of the PER samples has it
+  int ku, kl;
+
+  __device__ __forceinline__ void member(int k, bool up, bool low) {
+    if (FLAGS) {
+      mu = (mu & ~(1u << k)) | (up ? 1u << k : 0u);
+      ml = (ml & ~(1u << k)) | (low ? 1u << k : 0u);
+    } else {
+      pu[FLAGS ? 0 : k] = up ? 0.0 : INFINITY;
+      pl[FLAGS ? 0 : k] = low ? 0.0 : -INFINITY;
+    }
+  }
+  __device__ __forceinline__ bool in_low(int k) const { return FLAGS ? ((ml >> k) & 1u) != 0 : pl[FLAGS ? 0 : k] == 0.0; }
+  __device__ __forceinline__ void start() { bu = INFINITY; bl = -INFINITY; ku = kl = 0; }
+  __device__ __forceinline__ void offer(int k) {
+    double u, l;
+    if (FLAGS) {
+      const double v = f[k] + 0.0;
+      u = (mu >> k) & 1u ? v : INFINITY;
+      l = (ml >> k) & 1u ? v : -INFINITY;
+    } else {
+      u = f[k] + pu[FLAGS ? 0 : k];
+      l = f[k] + pl[FLAGS ? 0 : k];
+    }
+    ku = u < bu ? k : ku;
+    bu = u < bu ? u : bu;
+    kl = l > bl ? k : kl;
+    bl = l > bl ? l : bl;
+  }
+  // The wave's two winners to r (local index base + thread + k BS).  Every lane picks the
+  // multiplier and label of its own candidates, in the shadow of the reduction's rounds.
+  __device__ __forceinline__ void put_wave(SelRec &r, int base) const {
+    const int j = base + (int)threadIdx.x;
+    unsigned wu = (unsigned)(j + ku * BS), wl = (unsigned)(j + kl * BS);
+    wu = bu < INFINITY ? wu : (unsigned)IBIG;
+    wl = bl > -INFINITY ? wl : (unsigned)IBIG;
+    int lu, ll;
+    winner_lanes<64>(bu, wu, bl, wl, lu, ll);
+    double au = a[0], al = a[0];
+#pragma unroll
+    for (int k = 1; k < PER; ++k) {
+      au = ku == k ? a[k] : au;
+      al = kl == k ? a[k] : al;
+    }
+    wu |= (~ypos >> ku) << 31;  // (an empty side carries some label, which nobody reads)
+    wl |= (~ypos >> kl) << 31;
+    const int lane = threadIdx.x & 63;
+    if (lane == lu) { r.vu = bu; r.au = au; r.wu = wu; }
+    if (lane == ll) { r.vl = bl; r.al = al; r.wl = wl; }
+  }
+  // Sample j (uniform, of label y) of this workgroup's slice [base, base + cnt) has a new multiplier.
+  __device__ __forceinline__ void assign(int j, int base, int cnt, int y, double v, double C) {
+    const unsigned q = (unsigned)(j - base);
+    if (q >= (unsigned)cnt) return;
+    const bool mine = threadIdx.x == q % BS;
+    const bool up = y > 0 ? v < C : v > 0.0, low = y > 0 ? v > 0.0 : v < C;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {  // selects: branches on k would keep the arrays in scratch memory
+      const bool hit = mine && k == (int)(q / BS);
+      a[k] = hit ? v : a[k];
+      if (!FLAGS) {
+        pu[FLAGS ? 0 : k] = hit ? (up ? 0.0 : INFINITY) : pu[FLAGS ? 0 : k];
+        pl[FLAGS ? 0 : k] = hit ? (low ? 0.0 : -INFINITY) : pl[FLAGS ? 0 : k];
+      }
+    }
+    if (FLAGS) {
+      const unsigned bit = mine ? 1u << (q / BS) : 0u;
+      mu = up ? mu | bit : mu & ~bit;
+      ml = low ? ml | bit : ml & ~bit;
+    }
+  }
+};
 
 // ---------------------------------------------------------------------------------------
 // SO (Gram path): the second index of the pair by the second-order rule (p.second_order).
@@ -290,35 +508,43 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
   // Row path, dynamic LDS: dot products against x_u and x_l [2][per_wg] (fp64), cache tags
   // [cap], then the rows of X this workgroup keeps resident [res][d] (16-byte aligned).
   extern __shared__ float4 dyn4[];
-  __shared__ RecLds<Sel, NW> sh;
+  __shared__ SelLds<NW> sh;
   __shared__ RecLds<Sel2, NW> sh2;
   __shared__ int s_abort;
   __shared__ double s_kul;
   int buf = 0, buf2 = 0;
 
-  const int32_t pid = p.wg_prob[blockIdx.x];
+  const int32_t pid = __builtin_amdgcn_readfirstlane(p.wg_prob[blockIdx.x]);
   const Prob P = p.probs[pid];
   const int rank = (int)blockIdx.x - P.wg0;
   Ctl *ctl = P.ctl;
   if (ctl->status != ST_RUNNING) return;
-  int64_t t = ctl->t;
+  const int64_t t0 = ctl->t;
+  int64_t t = ((int64_t)__builtin_amdgcn_readfirstlane((int)(t0 >> 32)) << 32) |
+              (unsigned)__builtin_amdgcn_readfirstlane((int)t0);
   if (threadIdx.x == 0) s_abort = 0;
 
   const int64_t base = (int64_t)rank * P.per_wg;
   const int64_t lim = min(base + (int64_t)P.per_wg, P.n);
-  double f[PER], a[PER];
-  int yv[PER];
+  const double C = p.C;
+  Own<BS, PER, !GRAM> own;
+  own.ypos = own.mu = own.ml = 0;
+  unsigned col[PER];  // Gram path: byte offset of sample k's column in a row of the Gram
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int64_t j = base + threadIdx.x + (int64_t)k * BS;
+    const int64_t jc = min(j, lim - 1);  // past the end: some column, read and not used
+    if (GRAM) col[k] = (unsigned)(4 * gmap(P, jc));
     if (j < lim) {
-      f[k] = gp(P.f)[j];
-      a[k] = gp(P.alpha)[j];
-      yv[k] = label_of(P, j);
+      own.f[k] = gp(P.f)[j];
+      own.a[k] = gp(P.alpha)[j];
+      const bool pos = label_of(P, j) > 0;
+      own.ypos |= pos ? 1u << k : 0u;
+      own.member(k, pos ? own.a[k] < C : own.a[k] > 0.0, pos ? own.a[k] > 0.0 : own.a[k] < C);
     } else {
-      f[k] = 0.0;
-      a[k] = 0.0;
-      yv[k] = 0;
+      own.f[k] = 0.0;
+      own.a[k] = 0.0;
+      own.member(k, false, false);
     }
   }
 
@@ -349,38 +575,57 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
   }
   __syncthreads();
 
-  const double C = p.C;
   const int64_t t_end = min(t + p.steps, p.max_iter);
   // Candidates of this thread's samples; after the first scan they are gathered in the same
   // pass as the f update of the previous step.
-  Sel s;
-  sel_init(s);
+  own.start();
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int64_t j = base + threadIdx.x + (int64_t)k * BS;
-    if (j < lim) consider(s, f[k], a[k], yv[k], (int)j, C);
-  }
+  for (int k = 0; k < PER; ++k) own.offer(k);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // What the loop needs of the problem, in scalar registers (local samples and rows are below 2^31).
+  const int n = (int)P.n, nwg = P.nwg, len0 = (int)P.len0, cnt = (int)(lim - base);
+  const int64_t off0 = P.off0, off1 = P.off1 - P.len0, trace_len = P.trace_len;
+  const Xchg xc = xchg_of(P, rank);
   for (;;) {
     // 1. workgroup candidates
-    s = rec_block<Sel, NW>(rec_wave(s), sh, buf);
+    own.put_wave(sh.slot[buf][wave], (int)base);
+    Sel s = sel_combine<NW>(sh.slot[buf]);
+    buf ^= 1;
     // 2. exchange across the problem's workgroups (with the second-order rule every step has two
     // exchanges, stamped 2t + 1 and 2t + 2)
     const unsigned stamp1 = SO ? (unsigned)(2 * t + 1) : (unsigned)(t + 1);
-    if (P.nwg > 1) s = exchange<Sel, NW>(P, rank, stamp1, s, sh, buf, p.spin_limit, p.error, &s_abort);
-    const bool aborted = s_abort != 0;
-    // 3. stop rule
-    if (rank == 0 && threadIdx.x == 0 && t < P.trace_len) {
-      if (P.trace_ul) { P.trace_ul[2 * t] = s.iu; P.trace_ul[2 * t + 1] = s.il; }
-      if (P.trace_b) { P.trace_b[2 * t] = s.vu; P.trace_b[2 * t + 1] = s.vl; }
+    bool aborted = false;
+    if (nwg > 1) s = sel_exchange<NW>(xc, stamp1, s, sh, buf, p.spin_limit, p.error, &s_abort, aborted);
+    // The rows of the pair are on their way before anything else happens (an empty selection, which
+    // ends the launch below, reads row n - 1).
+    const int64_t u = min(s.iu, n - 1);
+    int64_t l = min(s.il, n - 1);
+    const int64_t gu = u + (u < len0 ? off0 : off1);
+    float ku[PER], kl[PER];
+    double kul = 0.0;
+    if (GRAM && !SO) {
+      const int64_t gl = l + (l < len0 ? off0 : off1);
+      const SVMX_GLOBAL char *Ru = gp(reinterpret_cast<const char *>(p.gram + gu * p.ld));
+      const SVMX_GLOBAL char *Rl = gp(reinterpret_cast<const char *>(p.gram + gl * p.ld));
+      kul = (double)*reinterpret_cast<const SVMX_GLOBAL float *>(Ru + 4 * gl);
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        unsigned c = col[k];
+        asm volatile("" : "+v"(c));  // stays a 32-bit offset to a scalar base
+        ku[k] = *reinterpret_cast<const SVMX_GLOBAL float *>(Ru + c);
+        kl[k] = *reinterpret_cast<const SVMX_GLOBAL float *>(Rl + c);
+      }
     }
-    int status = ST_RUNNING;
-    if (aborted) status = ST_TIMEOUT;
-    else if (s.iu == IBIG || s.il == IBIG || s.vl - s.vu <= p.tol) status = ST_CONVERGED;
-    else if (t >= p.max_iter) status = ST_MAXITER;
-    if (status != ST_RUNNING || t >= t_end) {
+    // 3. stop rule
+    if (t < trace_len && rank == 0 && threadIdx.x == 0) {
+      if (P.trace_ul) { gp(P.trace_ul)[2 * t] = s.iu; gp(P.trace_ul)[2 * t + 1] = s.il; }
+      if (P.trace_b) { gp(P.trace_b)[2 * t] = s.vu; gp(P.trace_b)[2 * t + 1] = s.vl; }
+    }
+    const bool done = s.iu == IBIG || s.il == IBIG || s.vl - s.vu <= p.tol;
+    if (__builtin_expect(aborted || done || t >= t_end, 0)) {
       if (rank == 0 && threadIdx.x == 0) {
         ctl->t = t;
-        ctl->status = status;
+        ctl->status = aborted ? ST_TIMEOUT : done ? ST_CONVERGED : t >= p.max_iter ? ST_MAXITER : ST_RUNNING;
         ctl->b_up = s.vu;
         ctl->b_low = s.vl;
         ctl->u = s.iu;
@@ -388,15 +633,14 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
       }
       break;
     }
-    const int64_t u = s.iu;
-    int64_t l = s.il;
-    const int64_t gu = gmap(P, u);
     double yl = (double)s.yl, fl = s.vl, al = s.al;
     const double yu = (double)s.yu;
 
     // 4. kernel rows of u and l for the own samples, K_ul, 2x2 solve, f update
-    float ku[PER], kl[PER];
-    double kul;
+    if (!GRAM || SO) {
+#pragma unroll
+      for (int k = 0; k < PER; ++k) ku[k] = kl[k] = 0.f;
+    }
     if (GRAM && SO) {
       // Second-order rule: row u first, the gains of the own members of I_low above b_up, a
       // second exchange for l (its record carries f_l, a_l, y_l and K(u, l)), then row l.
@@ -411,11 +655,11 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
         const int64_t j = base + threadIdx.x + (int64_t)k * BS;
-        const bool lo = (yv[k] > 0 && a[k] > 0.0) || (yv[k] < 0 && a[k] < C);
-        if (j < lim && lo && f[k] > s.vu) {
-          const double g = so_gain(f[k], s.vu, ku[k]);
+        if (own.in_low(k) && own.f[k] > s.vu) {
+          const double g = so_gain(own.f[k], s.vu, ku[k]);
           if (gt_max(g, (int)j, c.g, c.il)) {
-            c.g = g; c.fl = f[k]; c.al = a[k]; c.kul = (double)ku[k]; c.il = (int)j; c.yl = yv[k];
+            c.g = g; c.fl = own.f[k]; c.al = own.a[k]; c.kul = (double)ku[k]; c.il = (int)j;
+            c.yl = (own.ypos >> k) & 1u ? 1 : -1;
           }
         }
       }
@@ -446,21 +690,7 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
         if (j < lim) kl[k] = Rl[gmap(P, j)];
       }
       kul = c.il != IBIG ? c.kul : (double)Ru[gl];
-    } else if (GRAM) {
-      const int64_t gl = gmap(P, l);
-      const SVMX_GLOBAL float *Ru = gp(p.gram) + gu * p.ld;
-      const SVMX_GLOBAL float *Rl = gp(p.gram) + gl * p.ld;
-#pragma unroll
-      for (int k = 0; k < PER; ++k) {
-        const int64_t j = base + threadIdx.x + (int64_t)k * BS;
-        if (j < lim) {
-          const int64_t g = gmap(P, j);
-          ku[k] = Ru[g];
-          kl[k] = Rl[g];
-        }
-      }
-      kul = (double)Ru[gl];
-    } else {
+    } else if (!GRAM) {
       const int64_t gl = gmap(P, l);
       const int64_t d = p.d;
       const int gs = group_size_for(d, VEC4);
@@ -490,7 +720,6 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
       }
       if (!(hit_u && hit_l)) {
         typedef typename Lane<VEC4>::T T;
-        const int64_t cnt = lim - base;
         // Streamed samples [res, cnt) go in batches of SBS per group; the first batch of each
         // group is loaded before the resident samples are computed, so its HBM latency
         // overlaps that work.
@@ -556,16 +785,13 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
     const PairStep ps = solve_pair(C, s.vu, fl, s.au, al, yu, yl, kul);
     const double au_new = ps.au, al_new = ps.al;
     const double cu = (au_new - s.au) * yu, cl = (al_new - al) * yl;
-    sel_init(s);
+    own.assign((int)u, (int)base, cnt, s.yu, au_new, C);
+    own.assign((int)l, (int)base, cnt, l == s.il ? s.yl : (int)yl, al_new, C);
+    own.start();
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      const int64_t j = base + threadIdx.x + (int64_t)k * BS;
-      if (j < lim) {
-        f[k] = f_update(f[k], cu, ku[k], cl, kl[k]);
-        if (j == u) a[k] = au_new;
-        if (j == l) a[k] = al_new;
-        consider(s, f[k], a[k], yv[k], (int)j, C);
-      }
+      own.f[k] = f_update(own.f[k], cu, ku[k], cl, kl[k]);
+      own.offer(k);
     }
     ++t;
   }
@@ -574,8 +800,8 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
   for (int k = 0; k < PER; ++k) {
     const int64_t j = base + threadIdx.x + (int64_t)k * BS;
     if (j < lim) {
-      gp(P.f)[j] = f[k];
-      gp(P.alpha)[j] = a[k];
+      gp(P.f)[j] = own.f[k];
+      gp(P.alpha)[j] = own.a[k];
     }
   }
   if (use_cache) {
