@@ -56,21 +56,20 @@ constexpr int32_t WS_INNER_PER_Q = 100;   // and take at most 100 q pair steps
 // working_set = SVM_WORKING_SET_AUTO: for rows of 256 features or more q = 64 with a Gram (47.0
 // ms against 49.4 with q = 128 at 20,000 x 784) and 128 without (88.5 ms against 109.5 with
 // q = 64), else 32; the first WS_AUTO_PROBE_ROUNDS rounds decide.  The rounds go on when they took at least as many
-// pair steps per round as a round costs in pair steps (measured on MI355X: a round of q = 32
-// costs 4.4 to 6.2 pair steps on the Gram path -- 23.0 us against 5.22 at 100,000 x 32, 20.4
-// against 4.61 at 50,000 x 128, 25.1 against 4.05 at 20,000 x 784 -- and 4.7 on the row path
-// -- 38.7 us against 8.25 at 100,000 x 32; one of q = 128 9.9 to 18.1 on the Gram path -- 45.8
-// us against 4.61 at 50,000 x 128, 65.1 against 5.22 at 100,000 x 32, 73.4 against 4.05 at
-// 20,000 x 784 -- and about 11.4 on the row path, 135 us against 11.8 at 20,000 x 784), else
-// the pair solver takes over from the state the rounds reached.  Steps a round rise over a
-// training (at 100,000 x 32 from 6.5 in the first 128 rounds to 8.6 over all; on the
-// 50,000 x 128 mixture from 4.3 to 4.8), so the q = 32 thresholds sit a little under the
-// break-even of the problems that q is chosen for (rows of fewer than 256 features: 4.4 on the
-// Gram path, 4.7 on the row path); q = 128 keeps a margin above its 18.1.
+// pair steps per round as the thresholds below say, else the pair solver takes over from the state
+// the rounds reached.  The thresholds are the break-evens of an earlier build (4.4 for q = 32, 9.75
+// for q = 64 on the Gram path); now a round of q = 32 costs 5.3 to 6.9 pair steps (22.1 us against
+// 3.97 at 100,000 x 32, 19.4 against 3.66 at 50,000 x 128, 22.7 against 3.28 at 20,000 x 784), one of
+// q = 64 10.8 (35.5 us against 3.28 at 20,000 x 784), one of q = 128 10.6 on the row path (119 us
+// against 11.2).  They stay, because which schedule a problem gets is part of the result that
+// callers rely on; what lies in between loses little, for steps a round rise over a training
+// (100,000 x 32: 6.5 in the first 128 rounds, 8.6 over all; 40,000 x 16: below 4.75, then 6.5, rounds
+// 36.8 ms against 38.2 for the pair solver), except on the 50,000 x 128 mixture (4.3, then 4.8: 376
+// ms against 320).
 constexpr int64_t WS_AUTO_PROBE_ROUNDS = 128;
 double ws_auto_min_steps(int32_t q, bool gram) {
   if (q >= 128) return gram ? 20.0 : 12.5;
-  if (q >= 64) return gram ? 10.0 : 8.0;  // break-evens 9.75 (39.5 us against 4.05 at 20,000 x 784), 7.8
+  if (q >= 64) return gram ? 10.0 : 8.0;
   return gram ? 4.25 : 4.5;
 }
 

@@ -244,16 +244,14 @@ __device__ __forceinline__ PairStep solve_pair(double C, double bu, double bl, d
     L = fmax(0.0, au + al - C);
     H = fmin(C, au + al);
   }
-  double aln = al + yl * (bu - bl) / eta;
-  aln = aln < L ? L : (aln > H ? H : aln);
-  double aun = au + s * (al - aln);
-  aun = aun < 0.0 ? 0.0 : (aun > C ? C : aun);
+  // Clamps as max and min, and the two snaps side by side (a value cannot be within 1e-12 C of both
+  // bounds): the same values with a shorter chain, and the chain is what a step waits for.  (A
+  // zero's sign may differ before its snap; the snap makes it +0.)
+  const double aln = fmin(fmax(al + yl * (bu - bl) / eta, L), H);
+  const double aun = fmin(fmax(au + s * (al - aln), 0.0), C);
   const double snap = 1e-12 * C;
-  if (fabs(aln) <= snap) aln = 0.0;
-  if (fabs(aln - C) <= snap) aln = C;
-  if (fabs(aun) <= snap) aun = 0.0;
-  if (fabs(aun - C) <= snap) aun = C;
-  return PairStep{aun, aln};
+  const bool l0 = fabs(aln) <= snap, lC = fabs(aln - C) <= snap, u0 = fabs(aun) <= snap, uC = fabs(aun - C) <= snap;
+  return PairStep{u0 ? 0.0 : (uC ? C : aun), l0 ? 0.0 : (lC ? C : aln)};
 }
 
 // f_j + (c_u K_uj + c_l K_lj), rounded as written (no contraction), so that every solver

@@ -433,23 +433,6 @@ struct WsLds {
   int64_t steps;
 };
 
-// Min of a over each half of the wave (lanes 0 .. 31 and 32 .. 63), left in lanes 31 and 63:
-// the first five rounds of wave_minmax, the row-15 broadcast reaching rows 1 and 3 only.
-__device__ __forceinline__ void halves_min(double &a) {
-#define SVMX_HM_FULL(CTRL)                       \
-  {                                              \
-    const double oa = dpp_full_d<CTRL>(a);       \
-    a = oa < a ? oa : a;                         \
-  }
-  SVMX_HM_FULL(0xB1)   // quad_perm [1,0,3,2]
-  SVMX_HM_FULL(0x4E)   // quad_perm [2,3,0,1]
-  SVMX_HM_FULL(0x124)  // row_ror:4
-  SVMX_HM_FULL(0x128)  // row_ror:8
-#undef SVMX_HM_FULL
-  const double oa = dpp_mov_d<0x142, 0xA>(a);  // row_bcast:15 -> rows 1, 3
-  a = oa < a ? oa : a;
-}
-
 // The pair steps on B (wave 0 only; K_BB in S.u.K): S.bn receives the new multipliers,
 // S.steps the number of steps.  Lane l holds B positions l and l + 64.  The step is written
 // without lane-divergent branches, and the two wave reductions are independent chains that
@@ -470,8 +453,10 @@ __device__ __attribute__((noinline)) void local_solve(WsLds &S, double C, double
   double a0 = v0 ? S.ba[p0] : 0.0, a1 = v1 ? S.ba[p1] : 0.0;
   const int y0 = v0 ? S.by[p0] : 0, y1 = v1 ? S.by[p1] : 0;
   const int i0 = v0 ? S.bi[p0] : IBIG, i1 = v1 ? S.bi[p1] : IBIG;
-  const double tl = fmax(tol, frac * (b_low - b_up));
-  const int max_inner = (int)min<int64_t>(max_inner_p, max_iter - t);
+  // (uniform, and said so: the tests and branches of the loop stay scalar)
+  const double tl = uniform_d(fmax(tol, frac * (b_low - b_up)));
+  const int max_inner = __builtin_amdgcn_readfirstlane((int)min<int64_t>(max_inner_p, max_iter - t));
+  C = uniform_d(C);
   int inner = 0;
   for (; inner < max_inner; ++inner) {
     // this lane's best member of each side (positions l and l + 64)
@@ -488,22 +473,9 @@ __device__ __attribute__((noinline)) void local_solve(WsLds &S, double C, double
     const double cl_v = lo1 ? f1 : (l0 ? f0 : -INFINITY);
     const int cl_i = lo1 ? i1 : (l0 ? i0 : IBIG);
     const int cl_p = lo1 ? p1 : (l0 ? p0 : -1);
-    // wave extremes of both sides, then the smallest index among the lanes holding each
-    double ru = cu_v, rl = cl_v;
-    wave_minmax(ru, rl);
-    const unsigned long long tu = (unsigned long long)__ballot(cu_v == ru);
-    const unsigned long long tw = (unsigned long long)__ballot(cl_v == rl);
-    int lu = __ffsll(tu) - 1, ll = __ffsll(tw) - 1;
-    if (__popcll(tu) > 1) {
-      const int best = wave_min_int(cu_v == ru ? cu_i : IBIG);
-      lu = __ffsll((unsigned long long)__ballot(cu_v == ru && cu_i == best)) - 1;
-    }
-    if (__popcll(tw) > 1) {
-      const int best = wave_min_int(cl_v == rl ? cl_i : IBIG);
-      ll = __ffsll((unsigned long long)__ballot(cl_v == rl && cl_i == best)) - 1;
-    }
-    lu &= 63;
-    ll &= 63;
+    // the lanes of both winners (adding 0 turns -0 into the +0 it compares equal to)
+    int lu, ll;
+    winner_lanes<64>(cu_v + 0.0, (unsigned)cu_i, cl_v + 0.0, (unsigned)cl_i, lu, ll);
     const int pu = __builtin_amdgcn_readlane(cu_p, lu), pl = __builtin_amdgcn_readlane(cl_p, ll);
     if (pu < 0 || pl < 0) break;
     const double fu = readlane_d(cu_v, lu), fl = readlane_d(cl_v, ll);
@@ -535,7 +507,8 @@ __device__ __attribute__((noinline)) void local_solve(WsLds &S, double C, double
 // reductions finds both extremes (the smallest f in I_up and the largest in I_low, ties to the
 // smaller sample index: the choices of local_solve).  Both halves update their copy of every
 // member with the same arithmetic, so the copies stay equal and the steps are those of
-// local_solve.
+// local_solve.  The chain reduces the leading words of the values' order (order_words); the
+// rest is only looked at when members share one.
 __device__ __attribute__((noinline)) void local_solve_halves(WsLds &S, double C, double tol, double frac,
                                                             int64_t max_inner_p, int64_t max_iter, int m, double b_up,
                                                             double b_low, int64_t t) {
@@ -546,41 +519,47 @@ __device__ __attribute__((noinline)) void local_solve_halves(WsLds &S, double C,
   double a = v ? S.ba[p] : 0.0;
   const int y = v ? S.by[p] : 0;
   const int i = v ? S.bi[p] : IBIG;
-  const double tl = fmax(tol, frac * (b_low - b_up));
-  const int max_inner = (int)min<int64_t>(max_inner_p, max_iter - t);
+  // (uniform, and said so: the tests and branches of the loop stay scalar)
+  const double tl = uniform_d(fmax(tol, frac * (b_low - b_up)));
+  const int max_inner = __builtin_amdgcn_readfirstlane((int)min<int64_t>(max_inner_p, max_iter - t));
+  C = uniform_d(C);
   // membership as in ws_in_up / ws_in_low: I_up takes y > 0 with a < C or y < 0 with a > 0,
   // I_low the reverse; which label goes with which test is fixed for the lane
   const bool with_below_c = low ? y < 0 : y > 0, with_above_0 = low ? y > 0 : y < 0;
+  constexpr unsigned NONE = 0xffffffffu;  // above the leading word of any finite value
   int inner = 0;
   for (; inner < max_inner; ++inner) {
     const bool mem = (with_below_c & (a < C)) | (with_above_0 & (a > 0.0));
-    const double cv = mem ? (low ? -f : f) : INFINITY;
-    double r = cv;
-    halves_min(r);
-    const double ru = readlane_d(r, 31), rl = readlane_d(r, 63);  // rl = -(largest f in I_low)
-    const bool tie = low ? cv == rl : cv == ru;
-    unsigned long long tu = (unsigned long long)__ballot(cv == ru) & 0xffffffffull;
-    unsigned long long tw = (unsigned long long)__ballot(cv == rl) & ~0xffffffffull;
-    if (__popcll(tu) > 1) {
-      const int best = wave_min_int(!low && tie ? i : IBIG);
-      tu = (unsigned long long)__ballot(!low && tie && i == best);
+    unsigned hi, lo;
+    const double fz = f + 0.0;  // +0 for -0, which compares equal to it
+    order_words(low ? 0.0 - fz : fz, hi, lo);
+    hi = mem ? hi : NONE;
+    // min over each half, left in lanes 31 and 63
+    unsigned r = dpp_min_u32<0xB1>(hi);  // quad_perm [1,0,3,2]
+    r = dpp_min_u32<0x4E>(r);            // quad_perm [2,3,0,1]
+    r = dpp_min_u32<0x124>(r);           // row_ror:4
+    r = dpp_min_u32<0x128>(r);           // row_ror:8
+    r = dpp_min_u32_rows<0x142, 0xA>(r);  // row_bcast:15 -> rows 1, 3
+    const unsigned ru = (unsigned)__builtin_amdgcn_readlane((int)r, 31), rl = (unsigned)__builtin_amdgcn_readlane((int)r, 63);
+    if (ru == NONE || rl == NONE) break;
+    const unsigned long long tie = (unsigned long long)__ballot(hi == (low ? rl : ru));
+    const unsigned tu = (unsigned)tie, tw = (unsigned)(tie >> 32);
+    int pu, pl;
+    if (__builtin_expect(((tu & (tu - 1)) | (tw & (tw - 1))) == 0, 1)) {
+      pu = __builtin_ctz(tu);
+      pl = __builtin_ctz(tw);
+    } else {
+      pu = first_of<64>((unsigned long long)tu, lo, (unsigned)i);
+      pl = first_of<64>((unsigned long long)tw << 32, lo, (unsigned)i) - 32;
     }
-    if (__popcll(tw) > 1) {
-      const int best = wave_min_int(low && tie ? i : IBIG);
-      tw = (unsigned long long)__ballot(low && tie && i == best);
-    }
-    const int lu = (__ffsll(tu) - 1) & 63, ll = (__ffsll(tw) - 1) & 63;
-    const int cp = mem ? p : -1;
-    const int pu = __builtin_amdgcn_readlane(cp, lu), pl = __builtin_amdgcn_readlane(cp, ll);
-    if (pu < 0 || pl < 0) break;
-    const double fu = readlane_d(f, lu), fl = readlane_d(f, ll);
+    const double fu = readlane_d(f, pu), fl = readlane_d(f, pl);
     if (fl - fu <= tl) break;
-    const double au = readlane_d(a, lu), al = readlane_d(a, ll);
-    const double yu = (double)__builtin_amdgcn_readlane(y, lu);
-    const double yl = (double)__builtin_amdgcn_readlane(y, ll);
     const float *Ku = S.u.K + pu * WS_QMAX, *Kl = S.u.K + pl * WS_QMAX;
     const double kul = (double)Ku[pl];
     const float ku = Ku[p], kl = Kl[p];
+    const double au = readlane_d(a, pu), al = readlane_d(a, pl);
+    const double yu = (double)__builtin_amdgcn_readlane(y, pu);
+    const double yl = (double)__builtin_amdgcn_readlane(y, pl);
     const PairStep ps = solve_pair(C, fu, fl, au, al, yu, yl, kul);
     const double cu = (ps.au - au) * yu, cl = (ps.al - al) * yl;
     f = f_update(f, cu, ku, cl, kl);
