@@ -213,6 +213,52 @@ struct Layout {
   }
 };
 
+// What the host reads back after each solver launch, in one copy: the control blocks, the sums of
+// the finished problems, and the words that the start of a training clears.
+struct StatusLayout {
+  int64_t ctl, fin, ticket, error, check, rounds, bytes;  // offsets from the block's start
+  int64_t clear;                                          // the words from here on start as zeros
+};
+
+StatusLayout status_layout(int32_t P) {
+  StatusLayout l;
+  l.ctl = 0;
+  l.fin = l.ctl + (int64_t)sizeof(Ctl) * P;
+  l.clear = l.check = l.fin + 32LL * P;
+  l.rounds = l.check + (int64_t)sizeof(InputCheck);
+  l.error = l.rounds + 8;
+  l.ticket = l.error + 8;
+  l.bytes = l.ticket + 4LL * P;
+  return l;
+}
+
+struct Status {
+  StatusLayout l;
+  char *dev;
+  std::vector<char> host;
+  void place(int32_t P, char *base) {
+    l = status_layout(P);
+    dev = base;
+    host.assign(l.bytes, 0);
+  }
+  Ctl *d_ctl() const { return reinterpret_cast<Ctl *>(dev + l.ctl); }
+  double *d_fin() const { return reinterpret_cast<double *>(dev + l.fin); }
+  InputCheck *d_check() const { return reinterpret_cast<InputCheck *>(dev + l.check); }
+  int64_t *d_rounds() const { return reinterpret_cast<int64_t *>(dev + l.rounds); }
+  int32_t *d_error() const { return reinterpret_cast<int32_t *>(dev + l.error); }
+  int32_t *d_ticket() const { return reinterpret_cast<int32_t *>(dev + l.ticket); }
+  const Ctl &ctl(int32_t q) const { return reinterpret_cast<const Ctl *>(host.data() + l.ctl)[q]; }
+  const double *fin(int32_t q) const { return reinterpret_cast<const double *>(host.data() + l.fin) + 4 * q; }
+  const InputCheck &check() const { return *reinterpret_cast<const InputCheck *>(host.data() + l.check); }
+  int64_t rounds() const { return *reinterpret_cast<const int64_t *>(host.data() + l.rounds); }
+  int32_t error() const { return *reinterpret_cast<const int32_t *>(host.data() + l.error); }
+  hipError_t clear(hipStream_t s) { return hipMemsetAsync(dev + l.clear, 0, l.bytes - l.clear, s); }
+  hipError_t fetch(hipStream_t s) {
+    const hipError_t e = hipMemcpyAsync(host.data(), dev, l.bytes, hipMemcpyDeviceToHost, s);
+    return e != hipSuccess ? e : hipStreamSynchronize(s);
+  }
+};
+
 // ---------------------------------------------------------------------------- static scratch
 // The device workspace of svm_train_static: one array per device, alive until the process ends.
 // Its name is a host-side stand-in in host code; the device address comes from
@@ -233,8 +279,8 @@ struct TrainPlan {
   double auto_min_steps; // pair steps per round the probe must reach to keep the rounds
   Shape pair_shape;      // the pair solver's shape, for a switch
   int32_t cache_cap;
-  int64_t off_f, off_gram, off_split, off_sqn, off_cache, off_tags, off_ctl, off_prob, off_wgp, off_slots, off_slots2,
-      off_tul, off_tb, off_fin, off_err, off_rounds, off_warm;
+  int64_t off_f, off_gram, off_split, off_sqn, off_cache, off_tags, off_status, off_prob, off_wgp, off_slots, off_slots2,
+      off_tul, off_tb, off_part, off_warm;
   int64_t slot_words, slot2_words;
   int64_t total;
 };
@@ -296,7 +342,7 @@ svm_status plan_train(int64_t n, int64_t d, const Opts &o_in, TrainPlan *p) {
   p->off_sqn = p->gram ? -1 : L.add(8 * n);
   p->off_cache = p->cache_cap ? L.add(4LL * p->cache_cap * p->ld) : -1;
   p->off_tags = p->cache_cap ? L.add(4LL * p->cache_cap * p->shape.nwg) : -1;
-  p->off_ctl = L.add(sizeof(Ctl));
+  p->off_status = L.add(status_layout(1).bytes);
   p->off_prob = L.add(sizeof(Prob));
   p->off_wgp = L.add(4LL * std::max(p->shape.nwg + 1, p->auto_q ? p->pair_shape.nwg : 0));
   const int64_t per_rec = o.working_set > 0 ? ws_list_words() : SLOT_WORDS;
@@ -306,9 +352,7 @@ svm_status plan_train(int64_t n, int64_t d, const Opts &o_in, TrainPlan *p) {
   p->off_slots2 = L.add(8LL * p->slot2_words);
   p->off_tul = L.add(4LL * 2 * o.trace_len);
   p->off_tb = L.add(8LL * 2 * o.trace_len);
-  p->off_fin = L.add(8 * 4);
-  p->off_err = L.add(16);
-  p->off_rounds = L.add(8);
+  p->off_part = L.add(finalize_scratch_bytes(n, 1));
   p->off_warm = o.alpha_init ? L.add(12LL * n) : -1;  // warm start: support-vector list (coefs, indices)
   p->total = round_up(L.total, ALIGN);
   return SVM_OK;
@@ -322,25 +366,28 @@ uint64_t spin_ticks() {
   return (uint64_t)(SPIN_SECONDS * 1000.0 * (double)khz);
 }
 
-// A pair of HIP events on the launch stream; init(false) leaves it off (no events are created,
-// every record is a no-op and seconds() is 0), for the entry point that creates no resources.
-struct Timer {
-  hipEvent_t a = nullptr, b = nullptr;
-  ~Timer() {
-    if (a) (void)hipEventDestroy(a);
-    if (b) (void)hipEventDestroy(b);
+// HIP events on the launch stream between the phases of a training.  Off (no events are created,
+// every record is a no-op and the times are 0) for the entry point that creates no resources.
+struct Phases {
+  enum { GRAM, SOLVE, KERNEL, KERNEL_END, DONE, COUNT };
+  hipEvent_t ev[COUNT] = {};
+  bool on = false;
+  ~Phases() {
+    for (hipEvent_t e : ev)
+      if (e) (void)hipEventDestroy(e);
   }
-  hipError_t init(bool on = true) {
-    if (!on) return hipSuccess;
-    hipError_t e = hipEventCreate(&a);
-    if (e != hipSuccess) return e;
-    return hipEventCreate(&b);
+  hipError_t init(bool timed) {
+    on = timed;
+    for (int i = 0; on && i < COUNT; ++i) {
+      const hipError_t e = hipEventCreate(&ev[i]);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
-  hipError_t start(hipStream_t s) { return a ? hipEventRecord(a, s) : hipSuccess; }
-  hipError_t stop(hipStream_t s) { return b ? hipEventRecord(b, s) : hipSuccess; }
-  double seconds() {
+  hipError_t mark(int i, hipStream_t s) { return on ? hipEventRecord(ev[i], s) : hipSuccess; }
+  double seconds(int from, int to) {
     float ms = 0.f;
-    if (!a || !b || hipEventElapsedTime(&ms, a, b) != hipSuccess) return 0.0;
+    if (!on || hipEventElapsedTime(&ms, ev[from], ev[to]) != hipSuccess) return 0.0;
     return ms * 1e-3;
   }
 };
@@ -349,39 +396,51 @@ struct NeverStop {
   bool operator()() const { return false; }
 };
 
-// Launch a solver (launch(&max_coresident) enqueues one launch) until no problem is running,
-// or until stop() says so after a launch.  Returns SVM_OK or a negative status.
-template <class Launch, class Stop = NeverStop>
-svm_status run_launches(Launch launch, int32_t *error, int32_t nprob, int32_t total_wg, Ctl *d_ctl, hipStream_t stream,
-                        int32_t *launches, std::vector<Ctl> &h, double *t_kernel, bool timed = true,
-                        Stop stop = Stop()) {
-  int32_t herr = 0;
-  Timer tk;
-  HIPCHK(tk.init(timed));
-  h.assign(nprob, Ctl{});
+// What a training's launches share.
+struct Run {
+  Status st;
+  Phases ph;
+  hipStream_t stream;
+  int32_t launches = 0;
+  double t_kernel = 0.0;  // accumulates over the calls of one training
+};
+
+svm_status input_status(const Run &r, const int32_t *y);
+
+// Launch a solver (launch(&max_coresident) enqueues one launch, finish() what follows each) over
+// problems q0 .. q0 + nprob until none of them is running, or until stop() says so after a launch;
+// one copy and one wait a launch.  The first launch after the SOLVE mark is timed from that mark.
+// Returns SVM_OK or a negative status.
+template <class Launch, class Finish, class Stop = NeverStop>
+svm_status run_launches(Run &r, Launch launch, Finish finish, const int32_t *y, int32_t q0, int32_t nprob,
+                        int32_t total_wg, Stop stop = Stop()) {
   std::vector<int64_t> prev(nprob, -1);
   for (;;) {
     int32_t maxres = 0;
-    HIPCHK(tk.start(stream));
+    const int from = r.launches == 0 ? Phases::SOLVE : Phases::KERNEL;
+    if (from == Phases::KERNEL) HIPCHK(r.ph.mark(from, r.stream));
     hipError_t e = launch(&maxres);
     if (e == hipErrorCooperativeLaunchTooLarge)
       return fail(SVM_ENOMEM, "%d solver workgroups do not fit on the device at once (at most %d)", total_wg, maxres);
     if (e != hipSuccess) return fail(SVM_EDEVICE, "solver launch: %s", hipGetErrorString(e));
-    ++*launches;
-    HIPCHK(tk.stop(stream));
-    HIPCHK(hipMemcpyAsync(h.data(), d_ctl, sizeof(Ctl) * nprob, hipMemcpyDeviceToHost, stream));
-    HIPCHK(hipMemcpyAsync(&herr, error, sizeof(herr), hipMemcpyDeviceToHost, stream));
-    HIPCHK(hipStreamSynchronize(stream));
-    if (herr) return fail(SVM_EDEVICE, "a device-side wait exceeded its %.1f s limit", SPIN_SECONDS);
-    *t_kernel += tk.seconds();
+    ++r.launches;
+    HIPCHK(r.ph.mark(Phases::KERNEL_END, r.stream));
+    HIPCHK(finish());
+    HIPCHK(r.ph.mark(Phases::DONE, r.stream));
+    HIPCHK(r.st.fetch(r.stream));
+    const svm_status in = input_status(r, y);
+    if (in != SVM_OK) return in;
+    if (r.st.error()) return fail(SVM_EDEVICE, "a device-side wait exceeded its %.1f s limit", SPIN_SECONDS);
+    r.t_kernel += r.ph.seconds(from, Phases::KERNEL_END);
     bool running = false, progress = false;
     for (int32_t q = 0; q < nprob; ++q) {
-      if (h[q].status == ST_TIMEOUT)
+      const Ctl &c = r.st.ctl(q0 + q);
+      if (c.status == ST_TIMEOUT)
         return fail(SVM_EDEVICE, "a device-side wait exceeded its %.1f s limit (problem %d, step %lld)", SPIN_SECONDS, q,
-                    (long long)h[q].t);
-      if (h[q].status == ST_RUNNING) running = true;
-      if (h[q].t != prev[q]) progress = true;
-      prev[q] = h[q].t;
+                    (long long)c.t);
+      if (c.status == ST_RUNNING) running = true;
+      if (c.t != prev[q]) progress = true;
+      prev[q] = c.t;
     }
     if (!running) return SVM_OK;
     if (!progress) return fail(SVM_EDEVICE, "solver made no progress");
@@ -389,22 +448,28 @@ svm_status run_launches(Launch launch, int32_t *error, int32_t nprob, int32_t to
   }
 }
 
-// (*t_kernel accumulates over the calls of one training.)
-svm_status run_solver(SolveParams sp, int32_t nprob, int32_t total_wg, int32_t per_thread, bool gram, Ctl *d_ctl,
-                      hipStream_t stream, int32_t *launches, std::vector<Ctl> &h, double *t_kernel,
-                      bool timed = true) {
-  return run_launches([&](int32_t *maxres) { return launch_solver(sp, total_wg, per_thread, gram, stream, maxres); },
-                      sp.error, nprob, total_wg, d_ctl, stream, launches, h, t_kernel, timed);
+template <class Finish>
+svm_status run_solver(Run &r, const SolveParams &sp, Finish finish, const int32_t *y, int32_t q0, int32_t nprob,
+                      int32_t total_wg, int32_t per_thread, bool gram) {
+  return run_launches(
+      r, [&](int32_t *maxres) { return launch_solver(sp, total_wg, per_thread, gram, r.stream, maxres); }, finish, y, q0,
+      nprob, total_wg);
 }
 
-// EINVAL unless every value of X[0 .. count) is finite (a NaN or an infinity would leave no
-// stop test true, and the solver would run to max_iter).  flag: a cleared device word.
-svm_status check_finite(const float *X, int64_t count, int32_t *flag, hipStream_t stream) {
-  HIPCHK(launch_check_finite(X, count, flag, stream));
-  int32_t bad = 0;
-  HIPCHK(hipMemcpyAsync(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipStreamSynchronize(stream));
-  if (bad) return fail(SVM_EINVAL, "X holds a value that is not finite");
+// EINVAL for what the device found wrong with the input (labels first; a NaN or an infinity in X
+// would leave no stop test true, and the solver would run to max_iter).
+svm_status input_status(const Run &r, const int32_t *y) {
+  const InputCheck &c = r.st.check();
+  if (c.bad_label) {
+    const int64_t i = 0x7fffffffLL - c.bad_label;
+    int32_t v = 0;
+    HIPCHK(hipMemcpy(&v, y + i, sizeof(v), hipMemcpyDeviceToHost));
+    return fail(SVM_EINVAL, "label y[%lld] = %d is not +1 or -1", (long long)i, v);
+  }
+  if (c.both && (!c.pos || !c.neg))
+    return fail(SVM_EINVAL, "both classes must be present (%lld positive, %lld negative)", (long long)c.pos,
+                (long long)c.neg);
+  if (c.nonfinite) return fail(SVM_EINVAL, "X holds a value that is not finite");
   return SVM_OK;
 }
 
@@ -431,8 +496,8 @@ struct OvoPlan {
   bool gram;
   int64_t ld;
   int32_t P;
-  int64_t off_perm, off_xs, off_f, off_gram, off_split, off_sqn, off_ctl, off_prob, off_wgp, off_slots, off_slots2,
-      off_fin, off_err;
+  int64_t off_perm, off_xs, off_f, off_gram, off_split, off_sqn, off_status, off_prob, off_wgp, off_slots, off_slots2,
+      off_part;
   int64_t total;
 };
 
@@ -458,13 +523,12 @@ svm_status plan_ovo(int64_t n, int64_t d, int32_t k, const Opts &o, OvoPlan *p) 
   p->off_gram = p->gram ? L.add((int64_t)gram_bytes) : -1;
   p->off_split = (p->gram && o.gram_mfma == SVM_MFMA_SPLIT_F16) ? L.add(gram_split_scratch_bytes(n, d)) : -1;
   p->off_sqn = p->gram ? -1 : L.add(8 * n);
-  p->off_ctl = L.add((int64_t)sizeof(Ctl) * p->P);
+  p->off_status = L.add(status_layout(p->P).bytes);
   p->off_prob = L.add((int64_t)sizeof(Prob) * p->P);
   p->off_wgp = L.add(4LL * p->P * OVO_MAX_WG_PER_PAIR);
   p->off_slots = L.add(8LL * 2 * SLOT_WORDS * p->P * OVO_MAX_WG_PER_PAIR);
   p->off_slots2 = L.add(8LL * 2 * SLOT_WORDS * p->P * OVO_MAX_GROUPS);
-  p->off_fin = L.add(8LL * 4 * p->P);
-  p->off_err = L.add(16);
+  p->off_part = L.add(finalize_scratch_bytes(n, p->P));
   p->total = round_up(L.total, ALIGN);
   return SVM_OK;
 }
@@ -605,8 +669,10 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
   }
   const bool timed = !static_ws;
   hipStream_t stream = r.stream;
-  s0 = check_labels_pm1(y, n, stream);
-  if (s0 != SVM_OK) return s0;
+  if (r.alpha_init) {  // the host works with the labels below
+    s0 = check_labels_pm1(y, n, stream);
+    if (s0 != SVM_OK) return s0;
+  }
   // warm start: the given multipliers (and f) read to the host before anything writes alpha,
   // checked, and their support vectors listed for the device
   std::vector<double> warm_a, warm_f, warm_coef;
@@ -642,14 +708,14 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
   char *ws = static_cast<char *>(workspace);
   double *f = reinterpret_cast<double *>(ws + p.off_f);
   float *G = p.gram ? reinterpret_cast<float *>(ws + p.off_gram) : nullptr;
-  Ctl *ctl = reinterpret_cast<Ctl *>(ws + p.off_ctl);
+  Run run;
+  run.st.place(1, ws + p.off_status);
+  run.stream = stream;
   Prob *dprob = reinterpret_cast<Prob *>(ws + p.off_prob);
   int32_t *wgp = reinterpret_cast<int32_t *>(ws + p.off_wgp);
   u64 *slots = reinterpret_cast<u64 *>(ws + p.off_slots);
   int32_t *tul = reinterpret_cast<int32_t *>(ws + p.off_tul);
   double *tb = reinterpret_cast<double *>(ws + p.off_tb);
-  double *fin = reinterpret_cast<double *>(ws + p.off_fin);
-  int32_t *err = reinterpret_cast<int32_t *>(ws + p.off_err);
 
   Prob hp{};
   hp.n = n;
@@ -659,7 +725,7 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
   hp.y = y;
   hp.alpha = alpha;
   hp.f = f;
-  hp.ctl = ctl;
+  hp.ctl = run.st.d_ctl();
   hp.slots = slots;
   hp.trace_ul = r.trace_len ? tul : nullptr;
   hp.trace_b = r.trace_len ? tb : nullptr;
@@ -670,34 +736,29 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
   hp.g1 = p.shape.g1;
   hp.ng = p.shape.ng;
   hp.slots2 = (p.shape.g1 || p.working_set > 0) ? reinterpret_cast<u64 *>(ws + p.off_slots2) : nullptr;
-  std::vector<int32_t> hwgp(std::max(p.shape.nwg + 1, p.auto_q ? p.pair_shape.nwg : 0), 0);
-  HIPCHK(hipMemcpyAsync(dprob, &hp, sizeof(Prob), hipMemcpyHostToDevice, stream));
-  HIPCHK(hipMemcpyAsync(wgp, hwgp.data(), 4 * hwgp.size(), hipMemcpyHostToDevice, stream));
-  HIPCHK(hipMemsetAsync(err, 0, 16, stream));
-  s0 = check_finite(X, n * d, err + 2, stream);
-  if (s0 != SVM_OK) return s0;
+  // One launch writes the descriptor, initialises the state and checks the input; nobody waits for
+  // its verdict: the solvers leave at once on an invalid input, and the host reads it with their
+  // results.  The split-fp16 rows check X as they read it.
+  const bool split_reads = p.off_split >= 0;
+  HIPCHK(run.st.clear(stream));
+  HIPCHK(launch_train_prep(hp, dprob, wgp, std::max(p.shape.nwg + 1, p.auto_q ? p.pair_shape.nwg : 0), X,
+                           split_reads ? 0 : n * d, run.st.d_check(), stream));
   if (p.cache_cap)
     HIPCHK(hipMemsetAsync(ws + p.off_tags, 0xff, 4LL * p.cache_cap * p.shape.nwg, stream));
   const double t_upload = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
 
-  Timer tg, ts, tf;
-  HIPCHK(tg.init(timed));
-  HIPCHK(ts.init(timed));
-  HIPCHK(tf.init(timed));
-  HIPCHK(tg.start(stream));
+  HIPCHK(run.ph.init(timed));
+  HIPCHK(run.ph.mark(Phases::GRAM, stream));
   double *sqn = p.gram ? nullptr : reinterpret_cast<double *>(ws + p.off_sqn);
   if (p.gram && p.off_split >= 0)
-    HIPCHK(launch_gram_split(X, n, d, (float)gamma, G, p.ld, ws + p.off_split, stream));
+    HIPCHK(launch_gram_split(X, n, d, (float)gamma, G, p.ld, ws + p.off_split, stream, nullptr, run.st.d_check()));
   else if (p.gram)
     HIPCHK(launch_gram(X, n, d, (float)gamma, G, p.ld, stream));
   else if (p.working_set > 0)
-    HIPCHK(launch_split_rows(X, n, d, split_views(ws + p.off_split, n, d), stream));
+    HIPCHK(launch_split_rows(X, n, d, split_views(ws + p.off_split, n, d), stream, nullptr, run.st.d_check()));
   else
     HIPCHK(launch_row_norms(X, n, d, sqn, stream));
-  HIPCHK(tg.stop(stream));
 
-  HIPCHK(ts.start(stream));
-  HIPCHK(launch_solver_init(dprob, 1, n, stream));
   if (r.alpha_init) {
     HIPCHK(hipMemcpyAsync(alpha, warm_a.data(), 8 * n, hipMemcpyHostToDevice, stream));
     if (r.f_init) {
@@ -749,21 +810,22 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
     if (s0 != SVM_OK) return s0;
   }
   sp.spin_limit = spin_ticks();
-  sp.error = err;
-  int32_t launches = 0;
-  std::vector<Ctl> hc;
-  double t_kernel = 0.0;
-  int64_t *d_rounds = reinterpret_cast<int64_t *>(ws + p.off_rounds);
+  sp.error = run.st.d_error();
+  sp.check = run.st.d_check();
+  sp.alone = p.shape.nwg == 1 ? 1 : 0;
+  const auto finish = [&]() {
+    return launch_finalize(dprob, 1, n, C, reinterpret_cast<double *>(ws + p.off_part), run.st.d_ticket(), run.st.d_fin(),
+                           stream);
+  };
   svm_status s1;
   int32_t schedule = p.working_set > 0 ? 1 : 0;  // svm_stats.schedule
-  int64_t h_rounds = 0;
   if (p.working_set > 0) {
     HIPCHK(hipMemsetAsync(slots, 0, 8 * p.slot_words, stream));
     HIPCHK(hipMemsetAsync(ws + p.off_slots2, 0, 8 * p.slot2_words, stream));
-    HIPCHK(hipMemsetAsync(d_rounds, 0, 8, stream));
+    HIPCHK(run.ph.mark(Phases::SOLVE, stream));
     WsParams wp{};
     wp.sp = sp;
-    wp.rounds = d_rounds;
+    wp.rounds = run.st.d_rounds();
     wp.frac = WS_FRAC;
     wp.q = p.working_set;
     wp.max_inner = WS_INNER_PER_Q * p.working_set;
@@ -779,23 +841,17 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
       // the probe: the first WS_AUTO_PROBE_ROUNDS rounds (in as many launches as the host check
       // cadence makes), then the rule
       wp.round_end = WS_AUTO_PROBE_ROUNDS;
-      auto probed = [&]() {
-        if (hipMemcpy(&h_rounds, d_rounds, 8, hipMemcpyDeviceToHost) != hipSuccess) return true;
-        return h_rounds >= WS_AUTO_PROBE_ROUNDS;
-      };
-      s1 = run_launches(ws_launch, err, 1, nwg, ctl, stream, &launches, hc, &t_kernel, timed, probed);
+      auto probed = [&]() { return run.st.rounds() >= WS_AUTO_PROBE_ROUNDS; };
+      s1 = run_launches(run, ws_launch, finish, y, 0, 1, nwg, probed);
       if (s1 != SVM_OK) return s1;
-      if (hc[0].status == ST_RUNNING) {
-        HIPCHK(hipMemcpy(&h_rounds, d_rounds, 8, hipMemcpyDeviceToHost));
-        go_on = (double)hc[0].t >= p.auto_min_steps * (double)h_rounds;
-      } else {
-        go_on = false;  // solved within the probe
-      }
+      // else solved within the probe
+      go_on = run.st.ctl(0).status == ST_RUNNING &&
+              (double)run.st.ctl(0).t >= p.auto_min_steps * (double)run.st.rounds();
       wp.round_end = INT64_MAX;
     }
     if (go_on) {
-      s1 = run_launches(ws_launch, err, 1, nwg, ctl, stream, &launches, hc, &t_kernel, timed);
-    } else if (hc[0].status == ST_RUNNING) {
+      s1 = run_launches(run, ws_launch, finish, y, 0, 1, nwg);
+    } else if (run.st.ctl(0).status == ST_RUNNING) {
       // the pair solver takes over from the state the rounds left: f and alpha in the workspace
       // and the caller's alpha, the step count in the control block.  Its exchange words are
       // stamped so that no current stamp matches them (the next two steps read stamps t + 1
@@ -808,39 +864,35 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
       hp.ng = sh.ng;
       hp.slots2 = reinterpret_cast<u64 *>(ws + p.off_slots2);
       HIPCHK(hipMemcpyAsync(dprob, &hp, sizeof(Prob), hipMemcpyHostToDevice, stream));
-      const uint32_t stale = (uint32_t)((hc[0].t + 9) & 15) << 28;
+      const uint32_t stale = (uint32_t)((run.st.ctl(0).t + 9) & 15) << 28;
       HIPCHK(hipMemsetD32Async(reinterpret_cast<hipDeviceptr_t>(slots), stale, 2 * p.slot_words, stream));
       HIPCHK(hipMemsetD32Async(reinterpret_cast<hipDeviceptr_t>(ws + p.off_slots2), stale, 2 * p.slot2_words, stream));
       if (!p.gram) HIPCHK(launch_row_norms(X, n, d, sqn, stream));
       sp.max_per_wg = sh.per_wg;
       s0 = resident(sp, sh);
       if (s0 != SVM_OK) return s0;
-      s1 = run_solver(sp, 1, sh.nwg, sh.per_thread, p.gram, ctl, stream, &launches, hc, &t_kernel, timed);
+      sp.alone = sh.nwg == 1 ? 1 : 0;
+      s1 = run_solver(run, sp, finish, y, 0, 1, sh.nwg, sh.per_thread, p.gram);
     } else {
       s1 = SVM_OK;
     }
   } else {
-    s1 = run_solver(sp, 1, p.shape.nwg, p.shape.per_thread, p.gram, ctl, stream, &launches, hc, &t_kernel, timed);
+    HIPCHK(run.ph.mark(Phases::SOLVE, stream));
+    s1 = run_solver(run, sp, finish, y, 0, 1, p.shape.nwg, p.shape.per_thread, p.gram);
   }
   if (s1 != SVM_OK) return s1;
-  if (p.working_set > 0) HIPCHK(hipMemcpyAsync(&h_rounds, d_rounds, 8, hipMemcpyDeviceToHost, stream));
-  HIPCHK(ts.stop(stream));
+  const int64_t h_rounds = run.st.rounds();
 
-  HIPCHK(tf.start(stream));
-  HIPCHK(launch_finalize(dprob, 1, C, fin, stream));
-  double hfin[4];
-  HIPCHK(hipMemcpyAsync(hfin, fin, sizeof(hfin), hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipStreamSynchronize(stream));
   if (r.trace_len) {
-    const int64_t steps = std::min<int64_t>(r.trace_len, (p.working_set > 0 ? h_rounds : hc[0].t) + 1);
+    const int64_t steps = std::min<int64_t>(r.trace_len, (p.working_set > 0 ? h_rounds : run.st.ctl(0).t) + 1);
     if (r.trace_ws) HIPCHK(hipMemcpyAsync(r.trace_ws, tul, 4 * 2 * steps, hipMemcpyDeviceToHost, stream));
     if (r.trace_b) HIPCHK(hipMemcpyAsync(r.trace_b, tb, 8 * 2 * steps, hipMemcpyDeviceToHost, stream));
   }
   if (r.f_out) HIPCHK(hipMemcpyAsync(r.f_out, f, 8 * n, hipMemcpyDeviceToDevice, stream));
-  HIPCHK(tf.stop(stream));
-  HIPCHK(hipStreamSynchronize(stream));
+  if (r.f_out || r.trace_len) HIPCHK(hipStreamSynchronize(stream));
 
-  const Ctl &c = hc[0];
+  const Ctl &c = run.st.ctl(0);
+  const double *hfin = run.st.fin(0);
   *b = 0.5 * (c.b_up + c.b_low);
   if (st) {
     st->iterations = c.t;
@@ -850,12 +902,12 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
     st->b_low = c.b_low;
     st->dual_obj = 0.5 * hfin[0] - 0.5 * hfin[1];
     st->gram_used = p.gram ? 1 : 0;
-    st->launches = launches;
-    st->t_gram = tg.seconds();
-    st->t_solve = ts.seconds();
-    st->t_finalize = tf.seconds();
+    st->launches = run.launches;
+    st->t_gram = run.ph.seconds(Phases::GRAM, Phases::SOLVE);
+    st->t_solve = run.ph.seconds(Phases::SOLVE, Phases::KERNEL_END);
+    st->t_finalize = run.ph.seconds(Phases::KERNEL_END, Phases::DONE);
     st->t_total = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
-    st->t_kernel = t_kernel;
+    st->t_kernel = run.t_kernel;
     st->rounds = p.working_set > 0 ? h_rounds : 0;
     st->resident_rows = sp.res_rows;
     st->schedule = schedule;
@@ -964,13 +1016,14 @@ svm_status svm_train_ovo(const float *X, const int32_t *label, int64_t n, int64_
   float *Xs = reinterpret_cast<float *>(ws + p.off_xs);
   double *f = reinterpret_cast<double *>(ws + p.off_f);
   float *G = p.gram ? reinterpret_cast<float *>(ws + p.off_gram) : nullptr;
-  Ctl *ctl = reinterpret_cast<Ctl *>(ws + p.off_ctl);
+  Run run;
+  run.st.place(p.P, ws + p.off_status);
+  run.stream = stream;
+  Ctl *ctl = run.st.d_ctl();
   Prob *dprob = reinterpret_cast<Prob *>(ws + p.off_prob);
   int32_t *wgp = reinterpret_cast<int32_t *>(ws + p.off_wgp);
   u64 *slots = reinterpret_cast<u64 *>(ws + p.off_slots);
   u64 *slots2 = reinterpret_cast<u64 *>(ws + p.off_slots2);
-  double *fin = reinterpret_cast<double *>(ws + p.off_fin);
-  int32_t *err = reinterpret_cast<int32_t *>(ws + p.off_err);
 
   std::vector<Prob> hp(p.P);
   std::vector<int32_t> hwgp;
@@ -1058,27 +1111,27 @@ svm_status svm_train_ovo(const float *X, const int32_t *label, int64_t n, int64_
   HIPCHK(hipMemcpyAsync(dperm, perm.data(), 4 * n, hipMemcpyHostToDevice, stream));
   HIPCHK(hipMemcpyAsync(dprob, hp.data(), sizeof(Prob) * hp.size(), hipMemcpyHostToDevice, stream));
   HIPCHK(hipMemcpyAsync(wgp, hwgp.data(), 4 * hwgp.size(), hipMemcpyHostToDevice, stream));
-  HIPCHK(hipMemsetAsync(err, 0, 16, stream));
-  HIPCHK(launch_gather_rows(X, d, dperm, n, Xs, stream));
-  s0 = check_finite(X, n * d, err + 2, stream);  // its synchronisation also ends the class-sorted copy
-  if (s0 != SVM_OK) return s0;
+  HIPCHK(run.st.clear(stream));
+  HIPCHK(launch_solver_init(dprob, p.P, max_n, stream));
+  // The split-fp16 rows are read, checked and sorted by class in one pass; the other paths work on a
+  // class-sorted copy.
+  const bool split = p.gram && p.off_split >= 0;
+  if (!split) {
+    HIPCHK(launch_check_finite(X, n * d, run.st.d_check(), stream));
+    HIPCHK(launch_gather_rows(X, d, dperm, n, Xs, stream));
+  }
   const double t_upload = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
 
-  Timer tg, ts, tf;
-  HIPCHK(tg.init());
-  HIPCHK(ts.init());
-  HIPCHK(tf.init());
-  HIPCHK(tg.start(stream));
+  HIPCHK(run.ph.init(true));
+  HIPCHK(run.ph.mark(Phases::GRAM, stream));
   double *sqn = p.gram ? nullptr : reinterpret_cast<double *>(ws + p.off_sqn);
-  if (p.gram && p.off_split >= 0)
-    HIPCHK(launch_gram_split(Xs, n, d, (float)gamma, G, p.ld, ws + p.off_split, stream));
+  if (split)
+    HIPCHK(launch_gram_split(X, n, d, (float)gamma, G, p.ld, ws + p.off_split, stream, dperm, run.st.d_check()));
   else if (p.gram)
     HIPCHK(launch_gram(Xs, n, d, (float)gamma, G, p.ld, stream));
   else
     HIPCHK(launch_row_norms(Xs, n, d, sqn, stream));
-  HIPCHK(tg.stop(stream));
-  HIPCHK(ts.start(stream));
-  HIPCHK(launch_solver_init(dprob, p.P, max_n, stream));
+  HIPCHK(run.ph.mark(Phases::SOLVE, stream));
   SolveParams sp{};
   sp.probs = dprob;
   sp.wg_prob = wgp;
@@ -1095,53 +1148,49 @@ svm_status svm_train_ovo(const float *X, const int32_t *label, int64_t n, int64_
   sp.max_per_wg = max_per_wg;
   sp.second_order = r.selection == SVM_SELECT_SECOND_ORDER ? 1 : 0;
   sp.spin_limit = spin_ticks();
-  sp.error = err;
-  int32_t launches = 0;
-  std::vector<Ctl> hc;
-  double t_kernel = 0.0;
+  sp.error = run.st.d_error();
+  sp.check = run.st.d_check();
+  sp.alone = wg == p.P ? 1 : 0;
   int32_t woff = 0;
   for (size_t bi = 0; bi + 1 < bstart.size(); ++bi) {
+    const int32_t q0 = bstart[bi], np = bstart[bi + 1] - bstart[bi];
     SolveParams sb = sp;
-    sb.probs = dprob + bstart[bi];
+    sb.probs = dprob + q0;
     sb.wg_prob = wgp + woff;
-    std::vector<Ctl> hb;
-    int32_t lb = 0;
-    double tb = 0.0;
-    svm_status s1 = run_solver(sb, bstart[bi + 1] - bstart[bi], bwg[bi], per_thread, p.gram, ctl + bstart[bi], stream,
-                               &lb, hb, &tb);
+    const auto finish = [&]() {
+      return launch_finalize(dprob + q0, np, max_n, C,
+                             reinterpret_cast<double *>(ws + p.off_part) + 4LL * FINALIZE_BLOCKS_MAX * q0,
+                             run.st.d_ticket() + q0, run.st.d_fin() + 4LL * q0, stream);
+    };
+    const svm_status s1 = run_solver(run, sb, finish, nullptr, q0, np, bwg[bi], per_thread, p.gram);
     if (s1 != SVM_OK) return s1;
-    launches += lb;
-    t_kernel += tb;
-    hc.insert(hc.end(), hb.begin(), hb.end());
     woff += bwg[bi];
   }
-  HIPCHK(ts.stop(stream));
-  HIPCHK(tf.start(stream));
-  HIPCHK(launch_finalize(dprob, p.P, C, fin, stream));
-  std::vector<double> hfin(4 * (size_t)p.P);
-  HIPCHK(hipMemcpyAsync(hfin.data(), fin, 8 * hfin.size(), hipMemcpyDeviceToHost, stream));
-  HIPCHK(tf.stop(stream));
-  HIPCHK(hipStreamSynchronize(stream));
   bool maxed = false;
   const double t_total = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
+  const double t_gram = run.ph.seconds(Phases::GRAM, Phases::SOLVE);
+  const double t_solve = run.ph.seconds(Phases::SOLVE, Phases::KERNEL_END);
+  const double t_finalize = run.ph.seconds(Phases::KERNEL_END, Phases::DONE);
   for (int32_t q2 = 0; q2 < p.P; ++q2) {
-    b[q2] = 0.5 * (hc[q2].b_up + hc[q2].b_low);
-    maxed = maxed || hc[q2].status == ST_MAXITER;
+    const Ctl &c = run.st.ctl(q2);
+    const double *hfin = run.st.fin(q2);
+    b[q2] = 0.5 * (c.b_up + c.b_low);
+    maxed = maxed || c.status == ST_MAXITER;
     if (st) {
       svm_stats &S = st[q2];
-      S.iterations = hc[q2].t;
-      S.n_sv = (int64_t)hfin[4 * q2 + 2];
-      S.n_bound_sv = (int64_t)hfin[4 * q2 + 3];
-      S.b_up = hc[q2].b_up;
-      S.b_low = hc[q2].b_low;
-      S.dual_obj = 0.5 * hfin[4 * q2] - 0.5 * hfin[4 * q2 + 1];
+      S.iterations = c.t;
+      S.n_sv = (int64_t)hfin[2];
+      S.n_bound_sv = (int64_t)hfin[3];
+      S.b_up = c.b_up;
+      S.b_low = c.b_low;
+      S.dual_obj = 0.5 * hfin[0] - 0.5 * hfin[1];
       S.gram_used = p.gram ? 1 : 0;
-      S.launches = launches;
-      S.t_gram = tg.seconds();
-      S.t_solve = ts.seconds();
-      S.t_finalize = tf.seconds();
+      S.launches = run.launches;
+      S.t_gram = t_gram;
+      S.t_solve = t_solve;
+      S.t_finalize = t_finalize;
       S.t_total = t_total;
-      S.t_kernel = t_kernel;
+      S.t_kernel = run.t_kernel;
       S.rounds = 0;
       S.resident_rows = 0;
       S.schedule = 0;

@@ -32,17 +32,25 @@ __device__ __forceinline__ float split_rbf(float acc, float si, float sj, float 
   t = t > 0.f ? t : 0.f;
   return __builtin_amdgcn_exp2f(c * t);
 }
-hipError_t launch_split_rows(const float *X, int64_t n, int64_t d, const SplitX &s, hipStream_t st);
+// perm: row perm[r] of X becomes row r; chk: as launch_check_finite over the rows read.
+hipError_t launch_split_rows(const float *X, int64_t n, int64_t d, const SplitX &s, hipStream_t st,
+                             const int32_t *perm = nullptr, InputCheck *chk = nullptr);
 
 // Split-fp16 Gram (gram_split.hip): scratch bytes, and the build into G.
 int64_t gram_split_scratch_bytes(int64_t n, int64_t d);
 hipError_t launch_gram_split(const float *X, int64_t n, int64_t d, float gamma, float *G, int64_t ld, void *scratch,
-                             hipStream_t st);
+                             hipStream_t st, const int32_t *perm = nullptr, InputCheck *chk = nullptr);
 hipError_t launch_row_norms(const float *X, int64_t n, int64_t d, double *sqn, hipStream_t s);
-// flag[0] = 1 when a value of X[0 .. count) is not finite (flag left as it is otherwise).
-hipError_t launch_check_finite(const float *X, int64_t count, int32_t *flag, hipStream_t s);
+// chk->nonfinite = 1 when a value of X[0 .. count) is not finite (left as it is otherwise).
+hipError_t launch_check_finite(const float *X, int64_t count, InputCheck *chk, hipStream_t s);
 hipError_t launch_gather_rows(const float *X, int64_t d, const int32_t *perm, int64_t n, float *Xs, hipStream_t s);
+// Binary training: the descriptor P to dprob, wgp[0 .. nwgp) = 0, the state (alpha, f, exchange
+// words, control block) initialised, the labels P.y checked into chk (cleared before), and X[0 ..
+// count) as launch_check_finite.
+hipError_t launch_train_prep(const Prob &P, Prob *dprob, int32_t *wgp, int32_t nwgp, const float *X, int64_t count,
+                             InputCheck *chk, hipStream_t s);
 hipError_t launch_solver_init(const Prob *probs, int32_t nprob, int64_t max_n, hipStream_t s);
+hipError_t coresident_workgroups(const void *fn, int bs, size_t shmem, int *capacity);
 // total_wg <= 0 only reports in *max_coresident how many workgroups of the variant fit at once.
 hipError_t launch_solver(const SolveParams &p, int32_t total_wg, int32_t per_thread, bool gram, hipStream_t s,
                          int32_t *max_coresident);
@@ -50,7 +58,11 @@ hipError_t launch_solver(const SolveParams &p, int32_t total_wg, int32_t per_thr
 // LDS data (p's max_per_wg, cache_cap and d; per_thread as for launch_solver), or -1 on a HIP
 // error.
 int64_t solver_res_rows_max(const SolveParams &p, int32_t per_thread);
-hipError_t launch_finalize(const Prob *probs, int32_t nprob, double C, double *out /*[nprob][4]*/, hipStream_t s);
+// Sums of every problem that is not running any more to out [nprob][4]; part: scratch of
+// finalize_scratch_bytes, ticket [nprob]: zeros, left so.
+int64_t finalize_scratch_bytes(int64_t max_n, int32_t nprob);
+hipError_t launch_finalize(const Prob *probs, int32_t nprob, int64_t max_n, double C, double *part, int32_t *ticket,
+                           double *out, hipStream_t s);
 // One problem of a prediction launch: its training samples addressed like Prob (local j -> row
 // off0+j or off1+j-len0, then through perm when perm != NULL; labels from y by that row, or by
 // range), its multipliers alpha[alpha_off ..][ntr], where its support vectors and partial sums

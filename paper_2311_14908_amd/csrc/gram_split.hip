@@ -114,17 +114,20 @@ __global__ void __launch_bounds__(SBS, 4) gram_rbf_f16x3(SplitX s, int64_t n, fl
   if (!diag) store_tile_128<NT>(G, ld, n, i0 + wm * 64, j0 + wn * 64, kq, r16, kv);
 }
 
-hipError_t launch_split_rows(const float *X, int64_t n, int64_t d, const SplitX &s, hipStream_t st) {
+hipError_t launch_split_rows(const float *X, int64_t n, int64_t d, const SplitX &s, hipStream_t st, const int32_t *perm,
+                             InputCheck *chk) {
   if (n <= 0) return hipSuccess;
-  const SplitRows p = split_rows_of(X, n, s);
+  SplitRows p = split_rows_of(X, n, s);
+  p.perm = perm;
+  p.chk = chk;
   hipLaunchKernelGGL(gram_split_k, dim3((unsigned)split_rows_blocks(p)), dim3(256), 0, st, p, d);
   return hipGetLastError();
 }
 
 hipError_t launch_gram_split(const float *X, int64_t n, int64_t d, float gamma, float *G, int64_t ld, void *scratch,
-                             hipStream_t st) {
+                             hipStream_t st, const int32_t *perm, InputCheck *chk) {
   const SplitX s = split_views(scratch, n, d);
-  hipError_t e = launch_split_rows(X, n, d, s, st);
+  hipError_t e = launch_split_rows(X, n, d, s, st, perm, chk);
   if (e != hipSuccess) return e;
   const int64_t nt = (n + ST - 1) / ST;
   const int64_t ntiles = nt * (nt + 1) / 2;

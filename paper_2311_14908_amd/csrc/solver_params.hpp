@@ -36,6 +36,21 @@ struct Ctl {
   int64_t u, l;      // last selection
 };
 
+// What the device found out about a training's input.  The solvers leave at once when it is
+// invalid, so the host need not wait for it before it launches them.
+struct InputCheck {
+  int64_t pos, neg;   // labels +1 and -1 (binary training)
+  int32_t bad_label;  // 0, or 2^31 - 1 - index of the first label that is neither
+  int32_t nonfinite;  // 1: X holds a value that is not finite
+  int32_t both;       // 1: both labels must occur
+  int32_t pad;
+};
+
+__device__ __forceinline__ bool input_invalid(const InputCheck *c) {
+  const SVMX_GLOBAL InputCheck *g = gp(c);
+  return c != nullptr && (g->nonfinite != 0 || g->bad_label != 0 || (g->both != 0 && (g->pos == 0 || g->neg == 0)));
+}
+
 // One binary sub-problem of a solver launch.  A binary training run is one problem; a
 // one-vs-one run is one problem per class pair.  Local sample j maps to the global sample
 // (row of the Gram / of X) off0 + j for j < len0, else off1 + (j - len0).
@@ -58,6 +73,7 @@ struct Prob {
   int32_t pad;
 };
 
+constexpr int FINALIZE_BLOCKS_MAX = 24;  // workgroups that finalize one problem
 constexpr int SLOT_WORDS = 16;  // 6 used; a record sits alone in one 128-byte line
 
 // Rank that reduces the records (or merges the lists) of first-level group g, whose members are
@@ -93,6 +109,9 @@ struct SolveParams {
   int32_t second_order;    // Gram path: 1 = the second index of each pair by the second-order rule
   uint64_t spin_limit;     // wall-clock ticks (100 MHz) a wait may last
   int32_t *error;          // set to 1 on a wait time-out
+  const InputCheck *check; // of the training's input, or NULL
+  int32_t alone;           // 1: every problem of the launch has one workgroup
+  int32_t pad;
 };
 
 }  // namespace svmx

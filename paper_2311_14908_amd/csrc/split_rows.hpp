@@ -15,6 +15,8 @@ struct SplitRows {
   int64_t count;
   SplitX s;
   int32_t gs;
+  const int32_t *perm;  // position pos of s is row perm[pos] of X (NULL: the row itself)
+  InputCheck *chk;      // its nonfinite is set where a row read holds a value that is not finite
 };
 
 inline SplitRows split_rows_of(const float *X, int64_t count, const SplitX &s) {
@@ -22,6 +24,8 @@ inline SplitRows split_rows_of(const float *X, int64_t count, const SplitX &s) {
   r.X = X;
   r.count = count;
   r.s = s;
+  r.perm = nullptr;
+  r.chk = nullptr;
   r.gs = 1;
   while (r.gs < 64 && (int64_t)r.gs * 8 < s.dp) r.gs <<= 1;
   return r;
@@ -82,7 +86,7 @@ __device__ __forceinline__ void split_rows_block(const SplitRows &p, int64_t d, 
   for (int64_t r0 = block * per; r0 < p.count; r0 += blocks * per) {
     const int64_t r = row_of(r0 + mine < p.count ? r0 + mine : -1);
     const bool in = r >= 0;
-    const float *x = p.X + (in ? r : 0) * d;
+    const float *x = p.X + (in ? (p.perm ? (int64_t)p.perm[r] : r) : 0) * d;
     float v[SPLIT_KEEP][8];
     float m = 0.f;
     double q = 0.0;
@@ -126,6 +130,8 @@ __device__ __forceinline__ void split_rows_block(const SplitRows &p, int64_t d, 
     if (g == 0) {
       p.s.scale[r] = ldexpf(1.0f, e);
       p.s.nrm[r] = (float)q;
+      // squares of finite floats do not overflow an fp64 sum
+      if (p.chk && !__builtin_isfinite(q)) p.chk->nonfinite = 1;
     }
   }
 }

@@ -965,7 +965,7 @@ __global__ void __launch_bounds__(WS_BS) ws_solve(WsParams p) {
   const Prob P = sp.probs[pid];
   const int rank = (int)blockIdx.x - P.wg0;
   Ctl *ctl = P.ctl;
-  if (ctl->status != ST_RUNNING) return;
+  if (ctl->status != ST_RUNNING || input_invalid(sp.check)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double C = sp.C;
   const int h = p.q / 2;
@@ -1583,16 +1583,12 @@ hipError_t launch_ws_solver(const WsParams &p, int32_t total_wg, hipStream_t s, 
   else
     fn = p.sp.gram ? reinterpret_cast<const void *>(&ws_solve<true, 64>)
                    : reinterpret_cast<const void *>(&ws_solve<false, 64>);
-  int dev = 0, cus = 0, per_cu = 0;
-  hipError_t e = hipGetDevice(&dev);
+  int capacity = 0;
+  const hipError_t e = coresident_workgroups(fn, WS_BS, 0, &capacity);
   if (e != hipSuccess) return e;
-  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, WS_BS, 0);
-  if (e != hipSuccess) return e;
-  if (max_coresident) *max_coresident = per_cu * cus;
+  if (max_coresident) *max_coresident = capacity;
   if (total_wg <= 0) return hipSuccess;
-  if ((int64_t)total_wg > (int64_t)per_cu * cus) return hipErrorCooperativeLaunchTooLarge;
+  if (total_wg > capacity) return hipErrorCooperativeLaunchTooLarge;
   WsParams pp = p;
   void *args[] = {&pp};
   return hipLaunchCooperativeKernel(fn, dim3((unsigned)total_wg), dim3(WS_BS), args, 0, s);

@@ -52,6 +52,15 @@ class svm_stats(C.Structure):
         return {name: getattr(self, name) for name, _ in self._fields_}
 
 
+_STAT_NAMES = tuple(name for name, _ in svm_stats._fields_)
+_STAT_DTYPE = np.dtype(svm_stats)
+
+
+def _stat_dicts(array):
+    """A ctypes array of svm_stats as dicts, converted in one go."""
+    return [dict(zip(_STAT_NAMES, row)) for row in np.frombuffer(array, dtype=_STAT_DTYPE).tolist()]
+
+
 EXPORTS = ("svm_default_options", "svm_train_workspace_bytes", "svm_train", "svm_train_static",
            "svm_predict_workspace_bytes",
            "svm_predict", "svm_train_ovo_workspace_bytes", "svm_train_ovo", "svm_predict_ovo_workspace_bytes",
@@ -256,7 +265,7 @@ def svm_train_ovo(X, label, k: int, C_: float, gamma: float, tol: float, **opt) 
     status = _check(lib.svm_train_ovo(_ptr(X), _ptr(label), n, d, int(k), float(C_), float(gamma), float(tol),
                                       _ptr(alpha), b.ctypes.data_as(C.c_void_p), _ptr(ws), wsb, C.byref(o), st),
                     ok=(SVM_OK, SVM_NOT_CONVERGED))
-    return OvoOut(alpha=alpha, b=b, status=status, stats=[s.as_dict() for s in st])
+    return OvoOut(alpha=alpha, b=b, status=status, stats=_stat_dicts(st))
 
 
 def svm_predict_ovo(X, label, k: int, alpha, b: np.ndarray, gamma: float, X_test, **opt):
