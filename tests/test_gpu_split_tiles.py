@@ -88,6 +88,34 @@ def test_predict_edges(n, nsv, m, d, mfma):
     assert torch.equal(dec, again)
 
 
+@pytest.mark.parametrize("m", [1, 2, 4, 5, 15, 16, 17])
+@pytest.mark.parametrize("n,d", [(1, 1), (127, 5), (129, 16), (4097, 17), (513, 255), (700, 1024), (300, 1025), (9000, 2100)])
+def test_predict_few_samples(n, d, m):
+    """Up to 16 test samples in one pass over the rows, 17 by tiles: one and many chunks, lane groups of 1
+    to 64 lanes, rows past what a lane keeps, groups of four samples with a ragged last one; a pair of
+    a one-vs-one prediction gets the bits of that pair alone."""
+    X, T = _x(n, d, n + d), _x(m, d, m)
+    rng = np.random.default_rng(n)
+    y = torch.from_numpy(np.where(rng.random(n) < 0.5, 1, -1).astype(np.int32)).cuda()
+    alpha = torch.from_numpy(np.where(rng.random(n) < 0.6, rng.random(n), 0.0)).cuda()
+    dec = svmx.svm_predict(X, y, alpha, -0.5, 4.0 / d, T)
+    ref, tol = _decision64(X, y, alpha, -0.5, 4.0 / d, T)
+    assert float((dec - ref).abs().max()) <= tol
+    if n >= 127 and d <= 255:
+        k = 3
+        lab = (np.arange(n) % k).astype(np.int32)
+        al = torch.from_numpy(np.where(rng.random(2 * n) < 0.4, rng.random(2 * n), 0.0)).cuda()
+        b = np.array([0.1, -0.2, 0.3])
+        got, _ = svmx.svm_predict_ovo(X, torch.from_numpy(lab).cuda(), k, al, b, 4.0 / d, T)
+        offs, sizes = svmx.ovo_offsets(lab, k)
+        for p, (i, j) in enumerate(((0, 1), (0, 2), (1, 2))):
+            idx = np.concatenate([np.nonzero(lab == i)[0], np.nonzero(lab == j)[0]])
+            yy = torch.from_numpy(np.where(lab[idx] == i, 1, -1).astype(np.int32)).cuda()
+            one = svmx.svm_predict(X[torch.from_numpy(idx).cuda()].contiguous(), yy,
+                                   al[int(offs[p]):int(offs[p]) + int(sizes[p])].contiguous(), float(b[p]), 4.0 / d, T)
+            assert torch.equal(got[:, p].contiguous(), one)
+
+
 @pytest.mark.parametrize("k,per,m", [(2, 40, 3), (3, 5, 130), (12, 30, 70), (64, 3, 9)])
 def test_ovo_votes_are_those_of_its_decisions(k, per, m):
     """Ties and every vote count: the classes follow from the returned decision values."""
