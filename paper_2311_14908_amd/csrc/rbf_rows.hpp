@@ -13,7 +13,30 @@
 
 namespace svmx {
 
-// Feature positions (float4 units when VEC4) each lane of a group takes in the first register
+// How the lanes of a group read a row: one float a position (rows of fewer than 4 features), aligned
+// float4 units, or float4 units at any 4-byte address (rows whose length is no multiple of 4, or X off a
+// 16-byte boundary).  A row's last unit of the last kind ends at the row's end, so it overlaps the
+// unit before it; the features that the earlier unit has count as 0 in the row it is multiplied
+// with.  A step over rows of single floats is bound by its loads in flight and by a second block that
+// starts when the first is done (above 256 features); a quarter of the loads fetch the same lines.  Us
+// a step, single floats and float4 units at any address: 300,000 x 301 104 and 67 (3.5 and
+// 5.5 TB/s), 600,000 x 129 142 and 70, 500,000 x 102 61 and 35, 50,000 x 37 9.4 and 8.1.  Below 4
+// features a row has no whole unit.
+constexpr int ROW_SCALAR = 0, ROW_F4 = 1, ROW_F4U = 2;
+
+__host__ inline int row_kind_of(const float *X, int64_t d) {
+  if (d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0) return ROW_F4;
+  return d >= 4 ? ROW_F4U : ROW_SCALAR;
+}
+
+// Units of a row, and floats a row takes in LDS (there unit k is stored at 4k, so that LDS reads
+// are aligned whatever the row's length).
+__host__ __device__ __forceinline__ int64_t row_units(int64_t d, int kind) { return kind != ROW_SCALAR ? (d + 3) >> 2 : d; }
+__host__ __device__ __forceinline__ int64_t row_lds_pitch(int64_t d, int kind) {
+  return kind != ROW_SCALAR ? ((d + 3) >> 2) << 2 : d;
+}
+
+// Feature positions (float4 units unless ROW_SCALAR) each lane of a group takes in the first register
 // block of a row evaluation.
 constexpr int ROW_POSITIONS = 4;
 
@@ -21,8 +44,8 @@ constexpr int ROW_POSITIONS = 4;
 // units, at most 64 (longer rows continue in later blocks).  So a short row does not leave most
 // of a lane's positions masked: its lanes each take up to ROW_POSITIONS units, and a wave holds
 // 64 / gs samples at once.
-__host__ __device__ __forceinline__ int group_size_for(int64_t d, bool vec4) {
-  const int64_t units = vec4 ? (d + 3) / 4 : d;
+__host__ __device__ __forceinline__ int group_size_for(int64_t d, int kind) {
+  const int64_t units = row_units(d, kind);
   int gs = 1;
   while ((int64_t)ROW_POSITIONS * gs < units && gs < 64) gs <<= 1;
   return gs;
@@ -51,22 +74,67 @@ __device__ __forceinline__ double group_sum(double v, int gs) {
   return v;
 }
 
-// Per-lane operand type: a float4 of features when VEC4, else one float.
-template <bool VEC4> struct Lane;
-template <> struct Lane<true> {
+// Per-lane operand type T (a float4 of features, or one float) and accumulator type Acc.  load(row, k,
+// d): unit k of a row in memory, clamped to the last; mask(v, k, d): v without the features that
+// are not unit k's (all of them past the row's end).
+template <int V> struct Lane;
+template <> struct Lane<ROW_F4> {
   typedef float4 T;
-  static __device__ __forceinline__ float4 scale(float4 v, float m) { return make_float4(v.x * m, v.y * m, v.z * m, v.w * m); }
+  typedef float Acc;
+  static __device__ __forceinline__ float4 load(const float *row, int64_t k, int64_t d) {
+    const int64_t units = d >> 2;
+    return gp(reinterpret_cast<const float4 *>(row))[k < units ? k : units - 1];
+  }
+  static __device__ __forceinline__ float4 mask(float4 v, int64_t k, int64_t d) {
+    const float m = k < (d >> 2) ? 1.f : 0.f;
+    return make_float4(v.x * m, v.y * m, v.z * m, v.w * m);
+  }
   static __device__ __forceinline__ float dot(float4 v, float4 a, float acc) {
     acc = __builtin_fmaf(v.x, a.x, acc);
     acc = __builtin_fmaf(v.y, a.y, acc);
     acc = __builtin_fmaf(v.z, a.z, acc);
     return __builtin_fmaf(v.w, a.w, acc);
   }
+  static __device__ __forceinline__ double total(float acc) { return (double)acc; }
 };
-template <> struct Lane<false> {
+template <> struct Lane<ROW_SCALAR> {
   typedef float T;
-  static __device__ __forceinline__ float scale(float v, float m) { return v * m; }
+  typedef float Acc;
+  static __device__ __forceinline__ float load(const float *row, int64_t k, int64_t d) {
+    return gp(row)[k < d ? k : d - 1];
+  }
+  static __device__ __forceinline__ float mask(float v, int64_t k, int64_t d) { return v * (k < d ? 1.f : 0.f); }
   static __device__ __forceinline__ float dot(float v, float a, float acc) { return __builtin_fmaf(v, a, acc); }
+  static __device__ __forceinline__ double total(float acc) { return (double)acc; }
+};
+// Four fp32 sums a lane, one for each place of a unit, joined in fp64: an fp32 chain is then no longer
+// than one of single floats over the same row.
+template <> struct Lane<ROW_F4U> {
+  typedef float T __attribute__((ext_vector_type(4)));
+  typedef T Acc;
+  typedef float U __attribute__((ext_vector_type(4), aligned(4)));  // a float4 at any 4-byte address
+  static __device__ __forceinline__ T load(const float *row, int64_t k, int64_t d) {
+    const int64_t o = 4 * k < d - 4 ? 4 * k : d - 4;
+    return *(const SVMX_GLOBAL U *)(gp(row) + o);
+  }
+  static __device__ __forceinline__ T mask(T v, int64_t k, int64_t d) {
+    const int64_t c = 4 * k - (d - 4);  // features of the load that are not unit k's
+    v.x = c > 0 ? 0.f : v.x;
+    v.y = c > 1 ? 0.f : v.y;
+    v.z = c > 2 ? 0.f : v.z;
+    v.w = c > 3 ? 0.f : v.w;
+    return v;
+  }
+  static __device__ __forceinline__ T dot(T v, T a, T acc) {
+    acc.x = __builtin_fmaf(v.x, a.x, acc.x);
+    acc.y = __builtin_fmaf(v.y, a.y, acc.y);
+    acc.z = __builtin_fmaf(v.z, a.z, acc.z);
+    acc.w = __builtin_fmaf(v.w, a.w, acc.w);
+    return acc;
+  }
+  static __device__ __forceinline__ double total(T acc) {
+    return ((double)acc.x + (double)acc.y) + ((double)acc.z + (double)acc.w);
+  }
 };
 
 // Squared norm of row x, computed exactly as dot_batch computes the dot product of a sample
@@ -74,65 +142,62 @@ template <> struct Lane<false> {
 // increasing order in fp32, the group sums the partials in fp64).  So |x|^2 + |x|^2 - 2 x.x is
 // exactly 0 for identical rows (K = 1 on the diagonal and between duplicates), and every caller
 // gets the same bits for a row.
-template <bool VEC4>
+template <int V>
 __device__ __forceinline__ double sq_norm(const float *x, int64_t d, int lig, int gs) {
-  typedef typename Lane<VEC4>::T T;
-  const SVMX_GLOBAL T *p = gp(reinterpret_cast<const T *>(x));
-  const int64_t units = VEC4 ? (d >> 2) : d;
-  float acc = 0.f;
-  for (int64_t k = lig; k < units; k += gs) acc = Lane<VEC4>::dot(p[k], p[k], acc);
-  return group_sum((double)acc, gs);
+  const int64_t units = row_units(d, V);
+  typename Lane<V>::Acc acc = 0.f;
+  for (int64_t k = lig; k < units; k += gs) {
+    const typename Lane<V>::T v = Lane<V>::load(x, k, d);
+    acc = Lane<V>::dot(v, Lane<V>::mask(v, k, d), acc);
+  }
+  return group_sum(Lane<V>::total(acc), gs);
 }
 
 // Operands of a pair of rows (x_u, x_l) held by one lane for the first MAXM positions
-// k = lig + m*gs (float4 units when VEC4); positions past d are zeroed and masked.
-template <bool VEC4, int MAXM>
+// k = lig + m*gs (float4 units unless ROW_SCALAR); positions past d are zeroed and masked.
+template <int V, int MAXM>
 struct RowPair {
-  typename Lane<VEC4>::T a[MAXM], b[MAXM];
-  float mk[MAXM];  // 1 inside d, 0 past it
+  typename Lane<V>::T a[MAXM], b[MAXM];
 };
 
-template <bool VEC4, int MAXM>
-__device__ __forceinline__ void load_pair(RowPair<VEC4, MAXM> &r, const float *xu, const float *xl, int64_t d, int lig,
+template <int V, int MAXM>
+__device__ __forceinline__ void load_pair(RowPair<V, MAXM> &r, const float *xu, const float *xl, int64_t d, int lig,
                                           int gs) {
-  typedef typename Lane<VEC4>::T T;
-  const int64_t units = VEC4 ? (d >> 2) : d;
 #pragma unroll
   for (int m = 0; m < MAXM; ++m) {
     const int64_t k = lig + (int64_t)m * gs;
-    const int64_t kk = k < units ? k : units - 1;
-    r.mk[m] = k < units ? 1.f : 0.f;
-    r.a[m] = Lane<VEC4>::scale(gp(reinterpret_cast<const T *>(xu))[kk], r.mk[m]);
-    r.b[m] = Lane<VEC4>::scale(gp(reinterpret_cast<const T *>(xl))[kk], r.mk[m]);
+    r.a[m] = Lane<V>::mask(Lane<V>::load(xu, k, d), k, d);
+    r.b[m] = Lane<V>::mask(Lane<V>::load(xl, k, d), k, d);
   }
 }
 
 // Unit k of a sample row; XLDS: the row sits in LDS (the pointer is addressed as LDS, so the
 // load is an LDS read even where the compiler cannot trace the pointer to its array).
 // (The host pass of the compiler has no LDS address space and never runs this.)
-template <bool XLDS, typename T>
-__device__ __forceinline__ T row_unit(const float *row, int64_t k) {
+template <bool XLDS, int V>
+__device__ __forceinline__ typename Lane<V>::T row_unit(const float *row, int64_t k, int64_t d) {
 #if __HIP_DEVICE_COMPILE__
-  if constexpr (XLDS) return ((__attribute__((address_space(3))) const T *)row)[k];
+  if constexpr (XLDS) {
+    const int64_t units = row_units(d, V);
+    return ((__attribute__((address_space(3))) const typename Lane<V>::T *)row)[k < units ? k : units - 1];
+  }
 #endif
-  return gp(reinterpret_cast<const T *>(row))[k];
+  return Lane<V>::load(row, k, d);
 }
 
-// Block 0 of nb <= SB samples xs[0..nb): positions k = lig + m*gs, m < MAXM (float4 units when
-// VEC4), for one lane of a group of gs lanes.  Loads are unconditional (clamped positions and
+// Block 0 of nb <= SB samples xs[0..nb): positions k = lig + m*gs, m < MAXM (float4 units
+// unless ROW_SCALAR), for one lane of a group of gs lanes.  Loads are unconditional (clamped positions and
 // samples), so they issue back to back; the sample rows may sit in HBM or in LDS.
-template <bool VEC4, int SB, int MAXM, bool XLDS = false>
-__device__ __forceinline__ void load_block0(typename Lane<VEC4>::T (&v)[SB][MAXM], const float *const *xs, int nb,
+template <int V, int SB, int MAXM, bool XLDS = false>
+__device__ __forceinline__ void load_block0(typename Lane<V>::T (&v)[SB][MAXM], const float *const *xs, int nb,
                                             int64_t d, int lig, int gs) {
-  typedef typename Lane<VEC4>::T T;
-  const int64_t units = VEC4 ? (d >> 2) : d;
 #pragma unroll
   for (int s = 0; s < SB; ++s) {
     const float *row = xs[s < nb ? s : nb - 1];
 #pragma unroll
     for (int m = 0; m < MAXM; ++m) {
       const int64_t k = lig + (int64_t)m * gs;
-      v[s][m] = row_unit<XLDS, T>(row, k < units ? k : units - 1);
+      v[s][m] = row_unit<XLDS, V>(row, k, d);
     }
   }
 }
@@ -142,20 +207,21 @@ __device__ __forceinline__ void load_block0(typename Lane<VEC4>::T (&v)[SB][MAXM
 // products of its positions k = lig, lig+gs, ... in increasing order, so a sample's partials do
 // not depend on SB, on the batch it shares, on where its row is read from, or on which of the
 // two rows is x_u.
-template <bool VEC4, int SB, int MAXM, bool XLDS = false>
-__device__ __forceinline__ void dot_partials(const typename Lane<VEC4>::T (&v0)[SB][MAXM], const float *const *xs,
+template <int V, int SB, int MAXM, bool XLDS = false>
+__device__ __forceinline__ void dot_partials(const typename Lane<V>::T (&v0)[SB][MAXM], const float *const *xs,
                                              int nb, const float *xu, const float *xl, int64_t d, int lig, int gs,
-                                             const RowPair<VEC4, MAXM> &r, float (&fu)[SB], float (&fl)[SB]) {
-  typedef typename Lane<VEC4>::T T;
-  const int64_t units = VEC4 ? (d >> 2) : d;
+                                             const RowPair<V, MAXM> &r, typename Lane<V>::Acc (&fu)[SB],
+                                             typename Lane<V>::Acc (&fl)[SB]) {
+  typedef typename Lane<V>::T T;
+  const int64_t units = row_units(d, V);
 #pragma unroll
   for (int s = 0; s < SB; ++s) {
     fu[s] = 0.f;
     fl[s] = 0.f;
 #pragma unroll
     for (int m = 0; m < MAXM; ++m) {  // r.a / r.b are zero past d (X is finite)
-      fu[s] = Lane<VEC4>::dot(v0[s][m], r.a[m], fu[s]);
-      fl[s] = Lane<VEC4>::dot(v0[s][m], r.b[m], fl[s]);
+      fu[s] = Lane<V>::dot(v0[s][m], r.a[m], fu[s]);
+      fl[s] = Lane<V>::dot(v0[s][m], r.b[m], fl[s]);
     }
   }
   // Later blocks: MAXL positions at a time (fewer registers than block 0; they occur only for
@@ -163,24 +229,22 @@ __device__ __forceinline__ void dot_partials(const typename Lane<VEC4>::T (&v0)[
   constexpr int MAXL = MAXM > 2 ? 2 : MAXM;
   for (int64_t k0 = lig + (int64_t)gs * MAXM; k0 < units; k0 += (int64_t)gs * MAXL) {
     T a[MAXL], b[MAXL], v[SB][MAXL];
-    float mk[MAXL];
 #pragma unroll
     for (int m = 0; m < MAXL; ++m) {
       const int64_t k = k0 + (int64_t)m * gs;
-      const int64_t kk = k < units ? k : units - 1;
-      mk[m] = k < units ? 1.f : 0.f;
-      a[m] = gp(reinterpret_cast<const T *>(xu))[kk];
-      b[m] = gp(reinterpret_cast<const T *>(xl))[kk];
+      a[m] = Lane<V>::load(xu, k, d);
+      b[m] = Lane<V>::load(xl, k, d);
 #pragma unroll
-      for (int s = 0; s < SB; ++s) v[s][m] = row_unit<XLDS, T>(xs[s < nb ? s : nb - 1], kk);
+      for (int s = 0; s < SB; ++s) v[s][m] = row_unit<XLDS, V>(xs[s < nb ? s : nb - 1], k, d);
     }
 #pragma unroll
     for (int m = 0; m < MAXL; ++m) {
-      const T am = Lane<VEC4>::scale(a[m], mk[m]), bm = Lane<VEC4>::scale(b[m], mk[m]);
+      const int64_t k = k0 + (int64_t)m * gs;
+      const T am = Lane<V>::mask(a[m], k, d), bm = Lane<V>::mask(b[m], k, d);
 #pragma unroll
       for (int s = 0; s < SB; ++s) {
-        fu[s] = Lane<VEC4>::dot(v[s][m], am, fu[s]);
-        fl[s] = Lane<VEC4>::dot(v[s][m], bm, fl[s]);
+        fu[s] = Lane<V>::dot(v[s][m], am, fu[s]);
+        fl[s] = Lane<V>::dot(v[s][m], bm, fl[s]);
       }
     }
   }
@@ -189,17 +253,17 @@ __device__ __forceinline__ void dot_partials(const typename Lane<VEC4>::T (&v0)[
 // Dot products of nb <= SB samples xs[0..nb) with x_u (pu) and x_l (pl), computed by a group
 // of gs lanes: the lanes' fp32 partials (dot_partials) summed over the group in fp64
 // (group_sum).  Called with the whole wave active (nb, gs uniform per group).
-template <bool VEC4, int SB, int MAXM>
+template <int V, int SB, int MAXM>
 __device__ __forceinline__ void dot_batch(const float *const *xs, int nb, const float *xu, const float *xl, int64_t d,
-                                          int lig, int gs, const RowPair<VEC4, MAXM> &r, double *pu, double *pl) {
-  typename Lane<VEC4>::T v[SB][MAXM];
-  load_block0<VEC4, SB, MAXM>(v, xs, nb, d, lig, gs);
-  float fu[SB], fl[SB];
-  dot_partials<VEC4, SB, MAXM>(v, xs, nb, xu, xl, d, lig, gs, r, fu, fl);
+                                          int lig, int gs, const RowPair<V, MAXM> &r, double *pu, double *pl) {
+  typename Lane<V>::T v[SB][MAXM];
+  load_block0<V, SB, MAXM>(v, xs, nb, d, lig, gs);
+  typename Lane<V>::Acc fu[SB], fl[SB];
+  dot_partials<V, SB, MAXM>(v, xs, nb, xu, xl, d, lig, gs, r, fu, fl);
 #pragma unroll
   for (int s = 0; s < SB; ++s) {
-    pu[s] = group_sum((double)fu[s], gs);
-    pl[s] = group_sum((double)fl[s], gs);
+    pu[s] = group_sum(Lane<V>::total(fu[s]), gs);
+    pl[s] = group_sum(Lane<V>::total(fl[s]), gs);
   }
 }
 
@@ -233,14 +297,15 @@ __device__ __forceinline__ double swap_sum(double x, double y) {
 // the levels across rows and halves are lane swaps that also transpose: after level 16 the
 // lanes of even rows hold the u sums and those of odd rows the l sums, after level 32 the low
 // half holds sample s and the high half sample s + 1.  That halves the work of those levels.
-template <int SB>
-__device__ __forceinline__ void group_sums_store(const float (&fu)[SB], const float (&fl)[SB], int nb, int gs, int lig,
+template <int V, int SB>
+__device__ __forceinline__ void group_sums_store(const typename Lane<V>::Acc (&fu)[SB],
+                                                 const typename Lane<V>::Acc (&fl)[SB], int nb, int gs, int lig,
                                                  double *du, double *dl) {
   double u[SB], l[SB];
 #pragma unroll
   for (int s = 0; s < SB; ++s) {
-    u[s] = (double)fu[s];
-    l[s] = (double)fl[s];
+    u[s] = Lane<V>::total(fu[s]);
+    l[s] = Lane<V>::total(fl[s]);
     if (gs > 1) { u[s] += dpp_d<0xB1>(u[s]); l[s] += dpp_d<0xB1>(l[s]); }    // quad_perm [1,0,3,2]
     if (gs > 2) { u[s] += dpp_d<0x4E>(u[s]); l[s] += dpp_d<0x4E>(l[s]); }    // quad_perm [2,3,0,1]
     if (gs > 4) { u[s] += dpp_d<0x141>(u[s]); l[s] += dpp_d<0x141>(l[s]); }  // row_half_mirror

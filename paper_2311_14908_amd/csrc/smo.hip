@@ -498,13 +498,13 @@ struct Own {
 
 // ---------------------------------------------------------------------------------------
 // SO (Gram path): the second index of the pair by the second-order rule (p.second_order).
-template <int BS, int PER, bool GRAM, bool VEC4, bool ONE = false, bool SO = false>
+template <int BS, int PER, bool GRAM, int V, bool ONE = false, bool SO = false>
 __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
   constexpr int NW = BS / 64;
   // Samples per lane group and batch (a sample's arithmetic does not depend on them): scalar
   // lanes hold a quarter of the registers per sample, so they take twice as many; ONE: one at
   // a time (row_batch_one).
-  constexpr int SB = ONE ? 1 : VEC4 ? ROW_BATCH : 2 * ROW_BATCH;
+  constexpr int SB = ONE ? 1 : V != ROW_SCALAR ? ROW_BATCH : 2 * ROW_BATCH;
   // Row path, dynamic LDS: dot products against x_u and x_l [2][per_wg] (fp64), cache tags
   // [cap], then the rows of X this workgroup keeps resident [res][d] (16-byte aligned).
   extern __shared__ float4 dyn4[];
@@ -560,12 +560,12 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
     if (use_cache) {
       for (int s = threadIdx.x; s < p.cache_cap; s += BS) tags[s] = gp(p.cache_tags)[(size_t)blockIdx.x * p.cache_cap + s];
     }
-    typedef typename Lane<VEC4>::T T;
-    const int64_t units = VEC4 ? (p.d >> 2) : p.d;
+    typedef typename Lane<V>::T T;
+    const int64_t units = row_units(p.d, V);
     T *xr = reinterpret_cast<T *>(xres);
     for (int64_t e = threadIdx.x; e < res * units; e += BS) {
       const int64_t r = e / units, k = e - r * units;
-      xr[e] = gp(reinterpret_cast<const T *>(p.X + gmap(P, base + r) * p.d))[k];
+      xr[e] = Lane<V>::load(p.X + gmap(P, base + r) * p.d, k, p.d);
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -693,7 +693,7 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
     } else if (!GRAM) {
       const int64_t gl = gmap(P, l);
       const int64_t d = p.d;
-      const int gs = group_size_for(d, VEC4);
+      const int gs = group_size_for(d, V);
       const int lig = threadIdx.x & (gs - 1);
       const int ngroups = BS / gs;
       const int grp = threadIdx.x / gs;
@@ -701,7 +701,7 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
       // past it in batches of SB.
       const float *xu = p.X + gu * d, *xl = p.X + gl * d;
       const double nu = gp(p.sqn)[gu], nl = gp(p.sqn)[gl];
-      RowPair<VEC4, ROW_MAXM> rp;
+      RowPair<V, ROW_MAXM> rp;
       load_pair(rp, xu, xl, d, lig, gs);
       int su = -1, sl = -1;
       bool hit_u = false, hit_l = false;
@@ -715,15 +715,15 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
       if (grp == 0) {
         const float *xs1[1] = {xl};
         double pu1[1], pl1[1];
-        dot_batch<VEC4, 1, ROW_MAXM>(xs1, 1, xu, xl, d, lig, gs, rp, pu1, pl1);
+        dot_batch<V, 1, ROW_MAXM>(xs1, 1, xu, xl, d, lig, gs, rp, pu1, pl1);
         if (lig == 0) s_kul = (double)rbf_from_dot(nu, nl, pu1[0], p.gamma);
       }
       if (!(hit_u && hit_l)) {
-        typedef typename Lane<VEC4>::T T;
+        typedef typename Lane<V>::T T;
         // Streamed samples [res, cnt) go in batches of SBS per group; the first batch of each
         // group is loaded before the resident samples are computed, so its HBM latency
         // overlaps that work.
-        constexpr int SBS = ONE ? 1 : VEC4 ? ROW_SBATCH : 2 * ROW_SBATCH;
+        constexpr int SBS = ONE ? 1 : V != ROW_SCALAR ? ROW_SBATCH : 2 * ROW_SBATCH;
         const int64_t sstride = (int64_t)ngroups * SBS;
         int64_t qs = res + (int64_t)grp * SBS;
         int nbs = 0;
@@ -733,29 +733,29 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
           nbs = (int)min<int64_t>(SBS, cnt - qs);
 #pragma unroll
           for (int b = 0; b < SBS; ++b) xs[b] = p.X + gmap(P, base + qs + min(b, nbs - 1)) * d;
-          load_block0<VEC4, SBS, ROW_MAXM>(vs, xs, nbs, d, lig, gs);
+          load_block0<V, SBS, ROW_MAXM>(vs, xs, nbs, d, lig, gs);
         }
         for (int64_t q0 = (int64_t)grp * SB; q0 < res; q0 += (int64_t)ngroups * SB) {
           const int nb = (int)min<int64_t>(SB, res - q0);
           const float *xr[SB];
 #pragma unroll
-          for (int b = 0; b < SB; ++b) xr[b] = xres + (q0 + min(b, nb - 1)) * d;
+          for (int b = 0; b < SB; ++b) xr[b] = xres + (q0 + min(b, nb - 1)) * row_lds_pitch(d, V);
           T vr[SB][ROW_MAXM];
-          load_block0<VEC4, SB, ROW_MAXM, true>(vr, xr, nb, d, lig, gs);
-          float fu[SB], fl[SB];
-          dot_partials<VEC4, SB, ROW_MAXM, true>(vr, xr, nb, xu, xl, d, lig, gs, rp, fu, fl);
-          group_sums_store<SB>(fu, fl, nb, gs, lig, dotu + q0, dotl + q0);
+          load_block0<V, SB, ROW_MAXM, true>(vr, xr, nb, d, lig, gs);
+          typename Lane<V>::Acc fu[SB], fl[SB];
+          dot_partials<V, SB, ROW_MAXM, true>(vr, xr, nb, xu, xl, d, lig, gs, rp, fu, fl);
+          group_sums_store<V, SB>(fu, fl, nb, gs, lig, dotu + q0, dotl + q0);
         }
         while (qs < cnt) {
-          float fu[SBS], fl[SBS];
-          dot_partials<VEC4, SBS, ROW_MAXM>(vs, xs, nbs, xu, xl, d, lig, gs, rp, fu, fl);
-          group_sums_store<SBS>(fu, fl, nbs, gs, lig, dotu + qs, dotl + qs);
+          typename Lane<V>::Acc fu[SBS], fl[SBS];
+          dot_partials<V, SBS, ROW_MAXM>(vs, xs, nbs, xu, xl, d, lig, gs, rp, fu, fl);
+          group_sums_store<V, SBS>(fu, fl, nbs, gs, lig, dotu + qs, dotl + qs);
           qs += sstride;
           if (qs < cnt) {
             nbs = (int)min<int64_t>(SBS, cnt - qs);
 #pragma unroll
             for (int b = 0; b < SBS; ++b) xs[b] = p.X + gmap(P, base + qs + min(b, nbs - 1)) * d;
-            load_block0<VEC4, SBS, ROW_MAXM>(vs, xs, nbs, d, lig, gs);
+            load_block0<V, SBS, ROW_MAXM>(vs, xs, nbs, d, lig, gs);
           }
         }
       }
@@ -994,15 +994,13 @@ hipError_t launch_finalize(const Prob *probs, int32_t nprob, int64_t max_n, doub
   return hipGetLastError();
 }
 
+static int row_kind(const SolveParams &p) { return row_kind_of(p.X, p.d); }
+
 // Dynamic LDS of the row path: the fp64 dot products [2][per_wg], the cache tags, then `res`
 // resident rows of d floats from a 16-byte boundary.
 static size_t row_path_lds(const SolveParams &p, int64_t res) {
   const int64_t head = (16 * (int64_t)p.max_per_wg + 4 * (int64_t)p.cache_cap + 15) & ~(int64_t)15;
-  return (size_t)(head + 4 * res * p.d);
-}
-
-static bool row_vec4(const SolveParams &p) {
-  return (p.d % 4 == 0) && ((reinterpret_cast<uintptr_t>(p.X) & 15) == 0);
+  return (size_t)(head + 4 * res * row_lds_pitch(p.d, row_kind(p)));
 }
 
 // Row path, float4 lanes with 8 samples a thread: there batches of two samples spill registers.
@@ -1011,46 +1009,52 @@ static bool row_vec4(const SolveParams &p) {
 // 49.1); for wider groups the loads one batch keeps in flight matter more than the spill
 // (batches of one: 600,000 x 256 115 -> 120 us, x 512 214 -> 238, x 784 326 -> 362).
 static bool row_batch_one(const SolveParams &p, int32_t per_thread) {
-  return per_thread == 8 && row_vec4(p) && group_size_for(p.d, true) <= 8;
+  return per_thread == 8 && row_kind(p) != ROW_SCALAR && group_size_for(p.d, row_kind(p)) <= 8;
 }
 
-template <int BS, int PER, bool GRAM, bool VEC4, bool ONE = false, bool SO = false>
+template <int BS, int PER, bool GRAM, int V, bool ONE = false, bool SO = false>
 static const void *kernel_of() {
-  return reinterpret_cast<const void *>(&smo_solve<BS, PER, GRAM, VEC4, ONE, SO>);
+  return reinterpret_cast<const void *>(&smo_solve<BS, PER, GRAM, V, ONE, SO>);
 }
 
-// The solver variant for a path, samples per thread, (row path) float4 lanes and batches of
+// The solver variant for a path, samples per thread, (row path) the kind of units and batches of
 // one, (Gram path) the second-order rule; NULL if none.
-static const void *solver_kernel(bool gram, int32_t per_thread, bool vec4, bool one = false, bool so = false) {
+static const void *solver_kernel(bool gram, int32_t per_thread, int kind, bool one = false, bool so = false) {
   if (gram && so) {
     switch (per_thread) {
-      case 1: return kernel_of<BS_GRAM, 1, true, false, false, true>();
-      case 2: return kernel_of<BS_GRAM, 2, true, false, false, true>();
-      case 4: return kernel_of<BS_GRAM, 4, true, false, false, true>();
-      case 8: return kernel_of<BS_GRAM, 8, true, false, false, true>();
-      case 16: return kernel_of<BS_GRAM, 16, true, false, false, true>();
+      case 1: return kernel_of<BS_GRAM, 1, true, 0, false, true>();
+      case 2: return kernel_of<BS_GRAM, 2, true, 0, false, true>();
+      case 4: return kernel_of<BS_GRAM, 4, true, 0, false, true>();
+      case 8: return kernel_of<BS_GRAM, 8, true, 0, false, true>();
+      case 16: return kernel_of<BS_GRAM, 16, true, 0, false, true>();
       default: return nullptr;
     }
   }
   if (gram) {
     switch (per_thread) {
-      case 1: return kernel_of<BS_GRAM, 1, true, false>();
-      case 2: return kernel_of<BS_GRAM, 2, true, false>();
-      case 4: return kernel_of<BS_GRAM, 4, true, false>();
-      case 8: return kernel_of<BS_GRAM, 8, true, false>();
-      case 16: return kernel_of<BS_GRAM, 16, true, false>();
+      case 1: return kernel_of<BS_GRAM, 1, true, 0>();
+      case 2: return kernel_of<BS_GRAM, 2, true, 0>();
+      case 4: return kernel_of<BS_GRAM, 4, true, 0>();
+      case 8: return kernel_of<BS_GRAM, 8, true, 0>();
+      case 16: return kernel_of<BS_GRAM, 16, true, 0>();
       default: return nullptr;
     }
   }
-  switch (per_thread * 2 + (vec4 ? 1 : 0)) {
-    case 2: return kernel_of<BS_ROWS, 1, false, false>();
-    case 3: return kernel_of<BS_ROWS, 1, false, true>();
-    case 4: return kernel_of<BS_ROWS, 2, false, false>();
-    case 5: return kernel_of<BS_ROWS, 2, false, true>();
-    case 8: return kernel_of<BS_ROWS, 4, false, false>();
-    case 9: return kernel_of<BS_ROWS, 4, false, true>();
-    case 16: return kernel_of<BS_ROWS, 8, false, false>();
-    case 17: return one ? kernel_of<BS_ROWS, 8, false, true, true>() : kernel_of<BS_ROWS, 8, false, true>();
+  switch (per_thread * 4 + kind) {
+    case 1 * 4 + ROW_SCALAR: return kernel_of<BS_ROWS, 1, false, ROW_SCALAR>();
+    case 1 * 4 + ROW_F4: return kernel_of<BS_ROWS, 1, false, ROW_F4>();
+    case 1 * 4 + ROW_F4U: return kernel_of<BS_ROWS, 1, false, ROW_F4U>();
+    case 2 * 4 + ROW_SCALAR: return kernel_of<BS_ROWS, 2, false, ROW_SCALAR>();
+    case 2 * 4 + ROW_F4: return kernel_of<BS_ROWS, 2, false, ROW_F4>();
+    case 2 * 4 + ROW_F4U: return kernel_of<BS_ROWS, 2, false, ROW_F4U>();
+    case 4 * 4 + ROW_SCALAR: return kernel_of<BS_ROWS, 4, false, ROW_SCALAR>();
+    case 4 * 4 + ROW_F4: return kernel_of<BS_ROWS, 4, false, ROW_F4>();
+    case 4 * 4 + ROW_F4U: return kernel_of<BS_ROWS, 4, false, ROW_F4U>();
+    case 8 * 4 + ROW_SCALAR: return kernel_of<BS_ROWS, 8, false, ROW_SCALAR>();
+    case 8 * 4 + ROW_F4: return one ? kernel_of<BS_ROWS, 8, false, ROW_F4, true>()
+                              : kernel_of<BS_ROWS, 8, false, ROW_F4>();
+    case 8 * 4 + ROW_F4U: return one ? kernel_of<BS_ROWS, 8, false, ROW_F4U, true>()
+                              : kernel_of<BS_ROWS, 8, false, ROW_F4U>();
     default: return nullptr;
   }
 }
@@ -1086,7 +1090,7 @@ hipError_t coresident_workgroups(const void *fn, int bs, size_t shmem, int *capa
 hipError_t launch_solver(const SolveParams &p, int32_t total_wg, int32_t per_thread, bool gram, hipStream_t s,
                          int32_t *max_coresident) {
   if (p.second_order && !gram) return hipErrorInvalidValue;
-  const void *fn = solver_kernel(gram, per_thread, !gram && row_vec4(p), !gram && row_batch_one(p, per_thread),
+  const void *fn = solver_kernel(gram, per_thread, gram ? 0 : row_kind(p), !gram && row_batch_one(p, per_thread),
                                  p.second_order != 0);
   if (!fn) return hipErrorInvalidValue;
   const int bs = gram ? BS_GRAM : BS_ROWS;
@@ -1112,12 +1116,12 @@ int64_t solver_res_rows_max(const SolveParams &p, int32_t per_thread) {
   int dev = 0, max_lds = 0;
   if (hipGetDevice(&dev) != hipSuccess) return -1;
   if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return -1;
-  const void *fn = solver_kernel(false, per_thread, row_vec4(p), row_batch_one(p, per_thread));
+  const void *fn = solver_kernel(false, per_thread, row_kind(p), row_batch_one(p, per_thread));
   if (!fn) return -1;
   hipFuncAttributes attr;
   if (hipFuncGetAttributes(&attr, fn) != hipSuccess) return -1;
   const int64_t avail = (int64_t)max_lds - (int64_t)attr.sharedSizeBytes - (int64_t)row_path_lds(p, 0);
-  return avail > 0 ? avail / (4 * p.d) : 0;
+  return avail > 0 ? avail / (4 * row_lds_pitch(p.d, row_kind(p))) : 0;
 }
 
 }  // namespace svmx

@@ -1,0 +1,46 @@
+"""Row evaluations in float4 units at any 4-byte address: row lengths around a unit, a lane group and a
+register block, X on and off a 16-byte boundary."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [1, 3, 4, 5, 6, 7, 8, 15, 17, 18, 63, 64, 65, 127, 255, 256, 257, 301, 1021, 1025, 1026, 2051])
+@pytest.mark.parametrize("off", [0, 1])
+def test_rows_of_any_length_and_alignment(d, off):
+    """svm_kernel_rows against 64 bits, K = 1 exactly between equal rows, and one solver step (rows of X in LDS, then
+    all from memory) bit for bit as those values give it.
+
+    Bound: features in [0, 1) and gamma = 1/d, so gamma |x|^2 <= 1.  An fp32 chain of a lane has at most
+    4 ceil(units / lanes) roundings (the aligned float4 chain), each of 2^-24 of a sum of
+    non-negative products, so gamma d^2 is off by at most four times that, and K <= 1 is rounded once."""
+    from paper_2311_14908_amd import svmx
+    n = 700
+    g = torch.Generator().manual_seed(100 * d + off)
+    Xc = torch.rand(n, d, generator=g)
+    Xc[5] = Xc[n - 1]
+    buf = torch.full((n * d + off + 8,), 7.0, device="cuda")
+    X = buf[off:off + n * d].view(n, d)
+    X.copy_(Xc)
+    y = torch.where(torch.arange(n) % 2 == 0, 1, -1).to(torch.int32)
+    rows = np.array([5, n - 1, 0])
+    K = svmx.svm_kernel_rows(X, 1.0 / d, rows).cpu().numpy().astype(np.float64)
+    X64 = Xc.double().numpy()
+    ref = np.exp(-np.square(X64[None] - X64[rows][:, None]).sum(2) / d)
+    units = (d + 3) // 4
+    chain = 4 * max(4, -(-units // 64))
+    assert np.abs(K - ref).max() <= (4 * chain + 1) * 2.0 ** -24
+    assert K[0, 5] == 1.0 and K[0, n - 1] == 1.0 and K[2, 0] == 1.0
+    for res in (0, 1, -1):
+        f = torch.empty(n, dtype=torch.float64, device="cuda")
+        out = svmx.svm_train(X, y.cuda(), 1.0, 1.0 / d, 1e-3, gram=svmx.GRAM_OFF, max_iter=1, trace_len=1,
+                             resident_rows=res, f_out=f)
+        u, l = (int(v) for v in out.trace_ul[0])
+        Kp = svmx.svm_kernel_rows(X, 1.0 / d, np.array([u, l])).cpu().numpy().astype(np.float64)
+        a, yf = out.alpha.cpu().numpy(), y.numpy().astype(np.float64)
+        np.testing.assert_array_equal(f.cpu().numpy(), -yf + (a[u] * yf[u] * Kp[0] + a[l] * yf[l] * Kp[1]))
