@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "few_rule.hpp"
 #include "warm.hpp"
 #include "svmx.h"
 
@@ -558,8 +559,6 @@ svm_status class_sort(const int32_t *label, int64_t n, int32_t k, hipStream_t st
 // training samples each (n rows of X in all) and m test samples of d features, the compacted
 // support vectors, the partial sums, the problems' descriptions, and the split-fp16 rows of
 // both sets.
-constexpr int32_t PREDICT_PAIRS_MAX = 64;  // problems per prediction launch (bounds the partial sums)
-
 int64_t predict_scratch_bytes(int64_t n, int64_t ntr, int64_t pairs, int64_t m, int64_t d) {
   Layout L;
   L.add(4 * ntr * pairs);
@@ -972,6 +971,7 @@ svm_status svm_predict(const float *X_train, const int32_t *y, const double *alp
   L.gamma = gamma;
   L.split = r.gram_mfma == SVM_MFMA_SPLIT_F16;
   L.split_test_rows = L.split_train_rows = L.split;
+  L.few = predict_few_pays(1, n, n, d, m);
   L.dec = dec;
   L.dec_stride = 1;
   L.ws = predict_scratch(workspace, n, n, 1, m, d);
@@ -1228,7 +1228,7 @@ svm_status svm_predict_ovo(const float *X, const int32_t *label, int64_t n, int6
   if (s0 != SVM_OK) return s0;
   if (m == 0) return SVM_OK;
   int32_t *dperm = static_cast<int32_t *>(workspace);
-  const int32_t chunk = std::min<int32_t>(P, PREDICT_PAIRS_MAX);
+  const int32_t chunk = (int32_t)std::min<int64_t>(P, PREDICT_PAIRS_MAX);
   PredictLaunch L{};
   L.Xtr = X;
   L.T = X_test;
@@ -1239,6 +1239,7 @@ svm_status svm_predict_ovo(const float *X, const int32_t *label, int64_t n, int6
   L.alpha = alpha;
   L.gamma = gamma;
   L.split = r.gram_mfma == SVM_MFMA_SPLIT_F16;
+  L.few = predict_few_pays(P, (int64_t)(k - 1) * n, n, d, m);  // every sample is in k - 1 pairs
   L.dec_stride = P;
   L.ws = predict_scratch(static_cast<char *>(workspace) + round_up(4 * n, ALIGN), n, n, chunk, m, d);
   HIPCHK(hipMemcpyAsync(dperm, perm.data(), 4 * n, hipMemcpyHostToDevice, r.stream));

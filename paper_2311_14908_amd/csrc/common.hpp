@@ -91,7 +91,9 @@ struct PredictScratch {
 // for test sample q and problem p.  host_pairs: the problems; with more than one they must also
 // be on the device already, in ws.pairs.  split: the split-fp16 kernel; split_test_rows and
 // split_train_rows say which rows this launch splits first (n training positions, through perm;
-// all_train: all of them, else only support vectors of these problems).
+// all_train: all of them, else only support vectors of these problems).  few: one pass over the
+// training rows instead of tiles (predict_few_pays; the same for every launch of a prediction, since
+// later ones use the rows that the first has split).
 struct PredictLaunch {
   const float *Xtr, *T;
   int64_t n, d, m;
@@ -100,7 +102,7 @@ struct PredictLaunch {
   const int32_t *perm;
   const double *alpha;
   double gamma;
-  bool split, split_test_rows, split_train_rows, all_train;
+  bool split, split_test_rows, split_train_rows, all_train, few;
   double *dec;
   int64_t dec_stride;
   PredictScratch ws;

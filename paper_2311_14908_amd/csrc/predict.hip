@@ -12,7 +12,7 @@
 //    `gram_mfma = SVM_MFMA_F32` takes predict_mfma instead: v_mfma_f32_16x16x4f32, fp32 in, norms
 //    from the same LDS slabs.
 // 3. predict_final: dec = sum over splits (fixed order) - b, and the one-vs-one votes.
-// With at most 16 test samples one pass over the training rows (predict_few) takes the place of all
+// Few test samples (few_rule.hpp) take one pass over the training rows (predict_few) in place of all
 // of these.
 // Results are deterministic: no atomics touch values.
 #include "split_rows.hpp"
@@ -480,11 +480,11 @@ __global__ void __launch_bounds__(PBS, 3) predict_f16x3_k(SplitX st, int64_t m, 
 // t|^2) from the fp32 differences, squared and summed in fp64 (in fp32 the roundings of features
 // that are zero in most rows are the same for all of them and do not average out), and each row
 // group adds coef * K in fp64.  Bound by launches and by reading the support vectors once, for more
-// samples by the fp64 sums.  Up to FEW_MAX samples it is the faster way at every size measured: one
-// sample against 1,000 x 16 28 us a call (35 us by tiles), 8 against 5,000 x 100 37 (39), 1 against
-// 20,000 x 784 49 (106), 16 against 20,000 x 784 76 (107), against 50,000 x 300 79 (116), against
-// 50,000 x 8 44 (52); 32 against 20,000 x 784 take 124 (107).
-constexpr int FEW_MAX = 16, FEW_BS = 512, FEW_POS = 4;
+// samples, and for many problems that share rows, by the fp64 sums.  few_rule.hpp says when it is
+// taken.  Us a call of a binary prediction: one sample against 1,000 x 16 28 (35 by tiles), 8 against
+// 5,000 x 100 37 (39), 1 against 20,000 x 784 49 (106), 16 against 20,000 x 784 76 (107), against 50,000 x
+// 300 79 (116), against 50,000 x 8 44 (52); 32 against 20,000 x 784 take 124 (107).
+constexpr int FEW_BS = 512, FEW_POS = 4;
 
 // Chunks of a problem: about 8 rows for each row group to take one after the other; at most 64 and
 // one per 128 samples, so never more than predict_splits().
@@ -705,7 +705,7 @@ int predict_splits(int64_t m, int64_t nsv_max) {
 
 hipError_t launch_predict_pairs(const PredictLaunch &L, hipStream_t s) {
   if (L.m <= 0 || L.npairs <= 0) return hipSuccess;
-  if (L.m <= FEW_MAX) return launch_predict_few(L, s);
+  if (L.few) return launch_predict_few(L, s);
   const PredictScratch &ws = L.ws;
   PrepParams p{};
   p.alpha = L.alpha;

@@ -116,6 +116,32 @@ def test_predict_few_samples(n, d, m):
             assert torch.equal(got[:, p].contiguous(), one)
 
 
+@pytest.mark.parametrize("mfma", [svmx.MFMA_SPLIT_F16, svmx.MFMA_F32])
+@pytest.mark.parametrize("k,per,d,m", [(10, 130, 900, 16), (10, 1000, 784, 2), (12, 200, 1200, 16), (12, 200, 30, 16), (2, 300, 2000, 5)])
+def test_ovo_few_samples_either_way(k, per, d, m, mfma):
+    """Few samples of one-vs-one models that go by tiles (one launch of up to 64 pairs, and two that share the
+    split rows) or by the pass over the rows: every decision value against 64 bits."""
+    n = k * per
+    X, T = _x(n, d, n + d), _x(m, d, m)
+    lab = (np.arange(n) % k).astype(np.int32)
+    rng = np.random.default_rng(d)
+    al = torch.from_numpy(np.where(rng.random((k - 1) * n) < 0.3, rng.random((k - 1) * n), 0.0)).cuda()
+    b = rng.random(k * (k - 1) // 2)
+    dec, pred = svmx.svm_predict_ovo(X, torch.from_numpy(lab).cuda(), k, al, b, 4.0 / d, T, gram_mfma=mfma)
+    again, _ = svmx.svm_predict_ovo(X, torch.from_numpy(lab).cuda(), k, al, b, 4.0 / d, T, gram_mfma=mfma)
+    assert torch.equal(dec, again)
+    offs, sizes = svmx.ovo_offsets(lab, k)
+    p = 0
+    for i in range(k):
+        for j in range(i + 1, k):
+            idx = np.concatenate([np.nonzero(lab == i)[0], np.nonzero(lab == j)[0]])
+            yy = torch.from_numpy(np.where(lab[idx] == i, 1, -1)).cuda()
+            a = al[int(offs[p]):int(offs[p]) + int(sizes[p])]
+            ref, tol = _decision64(X[torch.from_numpy(idx).cuda()], yy, a, float(b[p]), 4.0 / d, T)
+            assert float((dec[:, p] - ref).abs().max()) <= tol, (i, j)
+            p += 1
+
+
 @pytest.mark.parametrize("k,per,m", [(2, 40, 3), (3, 5, 130), (12, 30, 70), (64, 3, 9)])
 def test_ovo_votes_are_those_of_its_decisions(k, per, m):
     """Ties and every vote count: the classes follow from the returned decision values."""
