@@ -188,8 +188,10 @@ int64_t svm_train_workspace_bytes(int64_t n, int64_t d, const svm_options *o);
  *   workspace/workspace_bytes          device scratch of at least svm_train_workspace_bytes
  *   o      options or NULL;  st  host stats out or NULL
  * EINVAL: n<2, d<1, non-finite or non-positive C/gamma/tol, NULL pointers, a label not in
- * {+1,-1} or only one class present, a value of X that is not finite (checked on the device
- * before any other work), byte counts of n*d or of the n^2 Gram that overflow int64.
+ * {+1,-1} or only one class present, a value of X that is not finite, byte counts of n*d or of the
+ * n^2 Gram that overflow int64.  Labels and values are checked on the device ahead of the work
+ * already queued behind them, which leaves at once on an invalid input; alpha and *b are then as
+ * they were.
  */
 svm_status svm_train(const float *X, const int32_t *y, int64_t n, int64_t d, double C, double gamma, double tol,
                      double *alpha, double *b, void *workspace, int64_t workspace_bytes, const svm_options *o,

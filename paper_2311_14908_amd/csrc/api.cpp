@@ -464,7 +464,8 @@ svm_status input_status(const Run &r, const int32_t *y) {
   if (c.bad_label) {
     const int64_t i = 0x7fffffffLL - c.bad_label;
     int32_t v = 0;
-    HIPCHK(hipMemcpy(&v, y + i, sizeof(v), hipMemcpyDeviceToHost));
+    HIPCHK(hipMemcpyAsync(&v, y + i, sizeof(v), hipMemcpyDeviceToHost, r.stream));
+    HIPCHK(hipStreamSynchronize(r.stream));
     return fail(SVM_EINVAL, "label y[%lld] = %d is not +1 or -1", (long long)i, v);
   }
   if (c.both && (!c.pos || !c.neg))
@@ -736,8 +737,9 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
   hp.ng = p.shape.ng;
   hp.slots2 = (p.shape.g1 || p.working_set > 0) ? reinterpret_cast<u64 *>(ws + p.off_slots2) : nullptr;
   // One launch writes the descriptor, initialises the state and checks the input; nobody waits for
-  // its verdict: the solvers leave at once on an invalid input, and the host reads it with their
-  // results.  The split-fp16 rows check X as they read it.
+  // its verdict: the Gram and the solvers leave at once on an invalid input, and the host reads it
+  // with their results.  Nothing has written to alpha by then.  The split-fp16 rows check X as they
+  // read it.
   const bool split_reads = p.off_split >= 0;
   HIPCHK(run.st.clear(stream));
   HIPCHK(launch_train_prep(hp, dprob, wgp, std::max(p.shape.nwg + 1, p.auto_q ? p.pair_shape.nwg : 0), X,
@@ -752,13 +754,17 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
   if (p.gram && p.off_split >= 0)
     HIPCHK(launch_gram_split(X, n, d, (float)gamma, G, p.ld, ws + p.off_split, stream, nullptr, run.st.d_check()));
   else if (p.gram)
-    HIPCHK(launch_gram(X, n, d, (float)gamma, G, p.ld, stream));
+    HIPCHK(launch_gram(X, n, d, (float)gamma, G, p.ld, stream, run.st.d_check()));
   else if (p.working_set > 0)
     HIPCHK(launch_split_rows(X, n, d, split_views(ws + p.off_split, n, d), stream, nullptr, run.st.d_check()));
   else
     HIPCHK(launch_row_norms(X, n, d, sqn, stream));
 
   if (r.alpha_init) {
+    // what has been launched so far has looked at all of the input; alpha is written only after its verdict
+    HIPCHK(run.st.fetch(stream));
+    s0 = input_status(run, y);
+    if (s0 != SVM_OK) return s0;
     HIPCHK(hipMemcpyAsync(alpha, warm_a.data(), 8 * n, hipMemcpyHostToDevice, stream));
     if (r.f_init) {
       HIPCHK(hipMemcpyAsync(f, warm_f.data(), 8 * n, hipMemcpyHostToDevice, stream));
@@ -812,6 +818,7 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
   sp.error = run.st.d_error();
   sp.check = run.st.d_check();
   sp.alone = p.shape.nwg == 1 ? 1 : 0;
+  sp.warm = r.alpha_init ? 1 : 0;
   const auto finish = [&]() {
     return launch_finalize(dprob, 1, n, C, reinterpret_cast<double *>(ws + p.off_part), run.st.d_ticket(), run.st.d_fin(),
                            stream);
@@ -1128,7 +1135,7 @@ svm_status svm_train_ovo(const float *X, const int32_t *label, int64_t n, int64_
   if (split)
     HIPCHK(launch_gram_split(X, n, d, (float)gamma, G, p.ld, ws + p.off_split, stream, dperm, run.st.d_check()));
   else if (p.gram)
-    HIPCHK(launch_gram(Xs, n, d, (float)gamma, G, p.ld, stream));
+    HIPCHK(launch_gram(Xs, n, d, (float)gamma, G, p.ld, stream, run.st.d_check()));
   else
     HIPCHK(launch_row_norms(Xs, n, d, sqn, stream));
   HIPCHK(run.ph.mark(Phases::SOLVE, stream));

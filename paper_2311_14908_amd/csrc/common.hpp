@@ -9,7 +9,9 @@
 namespace svmx {
 
 // Kernel launchers (defined in the .hip files).
-hipError_t launch_gram(const float *X, int64_t n, int64_t d, float gamma, float *G, int64_t ld, hipStream_t s);
+// (the Gram builds leave at once when chk says that the input is invalid)
+hipError_t launch_gram(const float *X, int64_t n, int64_t d, float gamma, float *G, int64_t ld, hipStream_t s,
+                       const InputCheck *chk = nullptr);
 hipError_t launch_kernel_rows(const float *X, int64_t n, int64_t d, double gamma, const int64_t *rows, int64_t r,
                               float *out, hipStream_t s);
 // Rows of X scaled by powers of two and split into two fp16 halves (gram_split.hip): row r is
@@ -44,8 +46,8 @@ hipError_t launch_row_norms(const float *X, int64_t n, int64_t d, double *sqn, h
 // chk->nonfinite = 1 when a value of X[0 .. count) is not finite (left as it is otherwise).
 hipError_t launch_check_finite(const float *X, int64_t count, InputCheck *chk, hipStream_t s);
 hipError_t launch_gather_rows(const float *X, int64_t d, const int32_t *perm, int64_t n, float *Xs, hipStream_t s);
-// Binary training: the descriptor P to dprob, wgp[0 .. nwgp) = 0, the state (alpha, f, exchange
-// words, control block) initialised, the labels P.y checked into chk (cleared before), and X[0 ..
+// Binary training: the descriptor P to dprob, wgp[0 .. nwgp) = 0, the state (f, exchange words,
+// control block) initialised, the labels P.y checked into chk (cleared before), and X[0 ..
 // count) as launch_check_finite.
 hipError_t launch_train_prep(const Prob &P, Prob *dprob, int32_t *wgp, int32_t nwgp, const float *X, int64_t count,
                              InputCheck *chk, hipStream_t s);

@@ -62,7 +62,8 @@ __device__ __forceinline__ void load_slab(const float *__restrict__ X, int64_t n
 // c = -gamma * log2(e) and t = |x_i|^2 + |x_j|^2 - 2 x_i.x_j clamped at 0 (v_exp_f32).
 template <bool VEC4, bool STORE4>
 __global__ void __launch_bounds__(GBS) gram_rbf_mfma(const float *__restrict__ X, int64_t n, int64_t d, float c,
-                                                     float *__restrict__ G, int64_t ld, int64_t nt, int64_t ntiles) {
+                                                     float *__restrict__ G, int64_t ld, int64_t nt, int64_t ntiles,
+                                                     const InputCheck *chk) {
   __shared__ float As[GKC][GPAD];
   __shared__ float Bs[GKC][GPAD];
   __shared__ float nA[GT], nB[GT];
@@ -70,7 +71,7 @@ __global__ void __launch_bounds__(GBS) gram_rbf_mfma(const float *__restrict__ X
   const int64_t per_xcd = (ntiles + 7) / 8;
   const int64_t b = (int64_t)blockIdx.x;
   const int64_t lin = (b % 8) * per_xcd + b / 8;
-  if (lin >= ntiles) return;
+  if (lin >= ntiles || input_invalid(chk)) return;
   int64_t ti, tj;
   upper_tile_super(lin, nt, ti, tj);
   const int64_t i0 = ti * GT, j0 = tj * GT;
@@ -146,7 +147,8 @@ __global__ void __launch_bounds__(GBS) gram_rbf_mfma(const float *__restrict__ X
   if (mirror) store_tile_128<STORE4>(G, ld, n, i0 + wm * 64, j0 + wn * 64, kq, r16, kv);
 }
 
-hipError_t launch_gram(const float *X, int64_t n, int64_t d, float gamma, float *G, int64_t ld, hipStream_t s) {
+hipError_t launch_gram(const float *X, int64_t n, int64_t d, float gamma, float *G, int64_t ld, hipStream_t s,
+                       const InputCheck *chk) {
   const int64_t nt = (n + GT - 1) / GT;
   const int64_t ntiles = nt * (nt + 1) / 2;
   const int64_t grid = ((ntiles + 7) / 8) * 8;
@@ -155,13 +157,17 @@ hipError_t launch_gram(const float *X, int64_t n, int64_t d, float gamma, float 
   const bool vec4 = (d % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
   const bool st4 = (ld % 4 == 0) && ((reinterpret_cast<uintptr_t>(G) & 15) == 0);
   if (vec4 && st4)
-    hipLaunchKernelGGL((gram_rbf_mfma<true, true>), dim3((unsigned)grid), dim3(GBS), 0, s, X, n, d, c, G, ld, nt, ntiles);
+    hipLaunchKernelGGL((gram_rbf_mfma<true, true>), dim3((unsigned)grid), dim3(GBS), 0, s, X, n, d, c, G, ld, nt, ntiles,
+                       chk);
   else if (vec4)
-    hipLaunchKernelGGL((gram_rbf_mfma<true, false>), dim3((unsigned)grid), dim3(GBS), 0, s, X, n, d, c, G, ld, nt, ntiles);
+    hipLaunchKernelGGL((gram_rbf_mfma<true, false>), dim3((unsigned)grid), dim3(GBS), 0, s, X, n, d, c, G, ld, nt, ntiles,
+                       chk);
   else if (st4)
-    hipLaunchKernelGGL((gram_rbf_mfma<false, true>), dim3((unsigned)grid), dim3(GBS), 0, s, X, n, d, c, G, ld, nt, ntiles);
+    hipLaunchKernelGGL((gram_rbf_mfma<false, true>), dim3((unsigned)grid), dim3(GBS), 0, s, X, n, d, c, G, ld, nt, ntiles,
+                       chk);
   else
-    hipLaunchKernelGGL((gram_rbf_mfma<false, false>), dim3((unsigned)grid), dim3(GBS), 0, s, X, n, d, c, G, ld, nt, ntiles);
+    hipLaunchKernelGGL((gram_rbf_mfma<false, false>), dim3((unsigned)grid), dim3(GBS), 0, s, X, n, d, c, G, ld, nt, ntiles,
+                       chk);
   return hipGetLastError();
 }
 

@@ -58,13 +58,13 @@ __global__ void __launch_bounds__(256) gram_split_k(SplitRows p, int64_t d) {
 // K(x_i, x_j) of i < j is always computed with x_i as the row operand.
 template <bool NT>
 __global__ void __launch_bounds__(SBS, 4) gram_rbf_f16x3(SplitX s, int64_t n, float c, float *__restrict__ G, int64_t ld,
-                                                      int64_t nt, int64_t ntiles, int64_t sup) {
+                                                      int64_t nt, int64_t ntiles, int64_t sup, const InputCheck *chk) {
   __shared__ SplitStage S;
   __shared__ float sA[ST], sB[ST], nA[ST], nB[ST];
   const int64_t per_xcd = (ntiles + 7) / 8;
   const int64_t b = (int64_t)blockIdx.x;
   const int64_t lin = (b % 8) * per_xcd + b / 8;
-  if (lin >= ntiles) return;
+  if (lin >= ntiles || input_invalid(chk)) return;
   int64_t ti, tj;
   upper_tile_super(lin, nt, ti, tj, sup);
   // (uniform by construction; said so, the store addresses stay in scalar registers)
@@ -146,9 +146,11 @@ hipError_t launch_gram_split(const float *X, int64_t n, int64_t d, float gamma, 
   // 2.37 ms at 50,000 x 128), 8 x 8 for longer rows (1.09 against 1.25 ms at 20,000 x 784)
   const int64_t sup = s.dp <= 4 * SKS ? 32 : 8;
   if (nt_store)
-    hipLaunchKernelGGL(gram_rbf_f16x3<true>, dim3((unsigned)grid), dim3(SBS), 0, st, s, n, c, G, ld, nt, ntiles, sup);
+    hipLaunchKernelGGL(gram_rbf_f16x3<true>, dim3((unsigned)grid), dim3(SBS), 0, st, s, n, c, G, ld, nt, ntiles, sup,
+                       chk);
   else
-    hipLaunchKernelGGL(gram_rbf_f16x3<false>, dim3((unsigned)grid), dim3(SBS), 0, st, s, n, c, G, ld, nt, ntiles, sup);
+    hipLaunchKernelGGL(gram_rbf_f16x3<false>, dim3((unsigned)grid), dim3(SBS), 0, st, s, n, c, G, ld, nt, ntiles, sup,
+                       chk);
   return hipGetLastError();
 }
 

@@ -527,6 +527,7 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
   const int64_t base = (int64_t)rank * P.per_wg;
   const int64_t lim = min(base + (int64_t)P.per_wg, P.n);
   const double C = p.C;
+  const bool from_zero = t == 0 && p.warm == 0;
   Own<BS, PER, !GRAM> own;
   own.ypos = own.mu = own.ml = 0;
   unsigned col[PER];  // Gram path: byte offset of sample k's column in a row of the Gram
@@ -537,7 +538,7 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
     if (GRAM) col[k] = (unsigned)(4 * gmap(P, jc));
     if (j < lim) {
       own.f[k] = gp(P.f)[j];
-      own.a[k] = gp(P.alpha)[j];
+      own.a[k] = from_zero ? 0.0 : gp(P.alpha)[j];
       const bool pos = label_of(P, j) > 0;
       own.ypos |= pos ? 1u << k : 0u;
       own.member(k, pos ? own.a[k] < C : own.a[k] > 0.0, pos ? own.a[k] > 0.0 : own.a[k] < C);
@@ -810,12 +811,9 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
   }
 }
 
-// One problem: a = 0, f = -y; exchange words and control block cleared.
+// One problem at a = 0 (which the solvers start from): f = -y; exchange words and control block cleared.
 __device__ __forceinline__ void init_problem(const Prob &P, int64_t i0, int64_t stride) {
-  for (int64_t j = i0; j < P.n; j += stride) {
-    P.alpha[j] = 0.0;
-    P.f[j] = -(double)label_of(P, j);
-  }
+  for (int64_t j = i0; j < P.n; j += stride) P.f[j] = -(double)label_of(P, j);
   for (int64_t q = i0; q < 2 * (int64_t)P.nwg * SLOT_WORDS; q += stride) P.slots[q] = 0ull;
   if (P.slots2)
     for (int64_t q = i0; q < 2 * (int64_t)P.ng * SLOT_WORDS; q += stride) P.slots2[q] = 0ull;

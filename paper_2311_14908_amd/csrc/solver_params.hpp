@@ -111,7 +111,8 @@ struct SolveParams {
   int32_t *error;          // set to 1 on a wait time-out
   const InputCheck *check; // of the training's input, or NULL
   int32_t alone;           // 1: every problem of the launch has one workgroup
-  int32_t pad;
+  int32_t warm;            // 0: a problem without a step starts from a = 0 and its alpha is not read, so
+                           // that a call refused for its input leaves the caller's alpha as it was
 };
 
 }  // namespace svmx

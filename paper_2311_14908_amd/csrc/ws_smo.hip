@@ -982,8 +982,9 @@ __global__ void __launch_bounds__(WS_BS) ws_solve(WsParams p) {
   // whichever entries a round leaves untouched
   u64 *kbuf = bcast + 2 * WS_BCAST_PITCH;
 
+  const bool from_zero = ctl->t == 0 && sp.warm == 0;
   for (int j = tid; j < len; j += WS_BS) {
-    const double fj = gp(P.f)[base + j], aj = gp(P.alpha)[base + j];
+    const double fj = gp(P.f)[base + j], aj = from_zero ? 0.0 : gp(P.alpha)[base + j];
     const int yj = ws_label(P, base + j);
     S.f[j] = fj;
     S.a[j] = aj;

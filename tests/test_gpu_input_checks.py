@@ -1,6 +1,8 @@
 """Input that only the device looks at: labels and values are checked there while the solve is already
 queued, and the call still refuses them; the sums over a problem's samples, taken by several
 workgroups, at the edges of their shares and when the solve is cut into many launches."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -42,6 +44,58 @@ def test_refused(n, kw):
     big.view(-1)[0] = 3e38  # finite, though its square is not
     assert svmx.svm_train(big, y, 1.0, 0.1, 1e-3, **kw).status == svmx.SVM_OK
     assert svmx.svm_train(X, y, 1.0, 0.1, 1e-3, **kw).status == svmx.SVM_OK
+
+
+def _refusals(X, y):
+    bad = y.clone()
+    bad[len(y) // 2] = 3
+    Xb = X.clone()
+    Xb.view(-1)[-1] = float("inf")
+    return ((X, bad), (X, torch.ones_like(y)), (Xb, y))
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(gram=svmx.GRAM_OFF), dict(gram_mfma=svmx.MFMA_F32), dict(working_set=8),
+                                dict(working_set=8, gram=svmx.GRAM_OFF), dict(working_set=-1),
+                                dict(selection=svmx.SELECT_SECOND_ORDER)])
+@pytest.mark.parametrize("n", [300, 5000])
+@pytest.mark.parametrize("warm", [False, True])
+def test_refused_leaves_the_outputs(n, warm, kw):
+    """A call refused for its labels or values has written neither alpha nor b, with and without a warm
+    start from another buffer."""
+    lib = svmx.load()
+    X, y = _problem(n, 7)
+    zero = torch.zeros(n, dtype=torch.float64, device="cuda")
+    o = svmx.options(alpha_init=zero if warm else None, **kw)
+    size = lib.svm_train_workspace_bytes(n, 7, C.byref(o))
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    for Xr, yr in _refusals(X, y):
+        alpha = torch.full((n,), 0.125, dtype=torch.float64, device="cuda")
+        b = C.c_double(7.0)
+        assert lib.svm_train(svmx._ptr(Xr), svmx._ptr(yr), n, 7, 1.0, 0.1, 1e-3, svmx._ptr(alpha), C.byref(b),
+                             svmx._ptr(ws), size, C.byref(o), None) == svmx.SVM_EINVAL
+        assert bool((alpha == 0.125).all()) and b.value == 7.0
+    # and a call that is not refused does not read it
+    ref = svmx.svm_train(X, y, 1.0, 0.1, 1e-3, **kw)
+    assert lib.svm_train(svmx._ptr(X), svmx._ptr(y), n, 7, 1.0, 0.1, 1e-3, svmx._ptr(alpha), C.byref(b), svmx._ptr(ws),
+                         size, C.byref(o), None) == svmx.SVM_OK
+    if not warm:
+        assert torch.equal(alpha, ref.alpha) and b.value == ref.b
+
+
+def test_refused_one_vs_one_leaves_the_outputs():
+    lib = svmx.load()
+    X, _ = _problem(600, 9)
+    X[-1, -1] = float("nan")
+    lab = (torch.arange(600, device="cuda") % 4).int()
+    for kw in (dict(), dict(gram=svmx.GRAM_OFF), dict(gram_mfma=svmx.MFMA_F32)):
+        o = svmx.options(**kw)
+        size = lib.svm_train_ovo_workspace_bytes(600, 9, 4, C.byref(o))
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        alpha = torch.full((1800,), 0.125, dtype=torch.float64, device="cuda")
+        b = np.full(6, 7.0)
+        assert lib.svm_train_ovo(svmx._ptr(X), svmx._ptr(lab), 600, 9, 4, 1.0, 0.1, 1e-3, svmx._ptr(alpha),
+                                 b.ctypes.data_as(C.c_void_p), svmx._ptr(ws), size, C.byref(o), None) == svmx.SVM_EINVAL
+        assert bool((alpha == 0.125).all()) and (b == 7.0).all()
 
 
 def test_refused_one_vs_one():
