@@ -707,6 +707,9 @@ hipError_t launch_predict_pairs(const PredictLaunch &L, hipStream_t s) {
   if (L.m <= 0 || L.npairs <= 0) return hipSuccess;
   if (L.few) return launch_predict_few(L, s);
   const PredictScratch &ws = L.ws;
+  // Items of one problem fit 32 bits (test tiles x splits, at most 3,072 more than the test tiles).
+  const int64_t nrt = (L.m + PT - 1) / PT;
+  if (nrt > 0x7fffffff - 4096) return hipErrorInvalidValue;
   PrepParams p{};
   p.alpha = L.alpha;
   p.pairs = L.npairs > 1 ? ws.pairs : nullptr;
@@ -738,8 +741,6 @@ hipError_t launch_predict_pairs(const PredictLaunch &L, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const float c = (float)(-L.gamma * 1.4426950408889634);
-  const int64_t nrt = (L.m + PT - 1) / PT;
-  if (nrt > 0x7fffffff / 512) return hipErrorInvalidValue;  // items of one problem: 32 bits
   int64_t items = 0;  // at most: the device counts the splits that have a tile
   for (int32_t q = 0; q < L.npairs; ++q) items += nrt * L.host_pairs[q].nsplit;
   if (L.split) {

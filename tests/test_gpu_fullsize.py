@@ -242,3 +242,21 @@ def test_rounds_past_the_lds_rows():
     f = oracle.f_from_alpha(X, y, a, wl.gamma)
     gap, W = kkt_and_gap(f, y, a, b, wl.C, wl.tol, slack=1e-4)
     assert abs(W - st["dual_obj"]) <= 1e-6 * abs(W)
+
+
+@pytest.mark.parametrize("mfma", [svmx.MFMA_SPLIT_F16, svmx.MFMA_F32])
+def test_predict_of_half_a_billion_samples(mfma):
+    """More test samples than 2^22 tiles of 128 (about 85 GB of workspace): every decision value.  Features in
+    [0, 1), so the exponent is off by at most a few roundings of fp32 and a kernel value by 1e-6."""
+    m = (1 << 29) + 130
+    g = torch.Generator("cuda").manual_seed(5)
+    T = torch.rand((m, 1), device="cuda", generator=g)
+    X = torch.tensor([[0.1], [0.5], [0.9]], device="cuda")
+    y = torch.tensor([1, -1, 1], dtype=torch.int32, device="cuda")
+    alpha = torch.tensor([0.75, 1.25, 0.5], dtype=torch.float64, device="cuda")
+    dec = svmx.svm_predict(X, y, alpha, 0.25, 2.0, T, gram_mfma=mfma)
+    coef = alpha * y.double()
+    for q in range(0, m, 1 << 26):
+        t = T[q:q + (1 << 26)].double()
+        ref = sum(c * torch.exp(-2.0 * (t[:, 0] - x) ** 2) for c, x in zip(coef, X[:, 0].double())) - 0.25
+        assert float((dec[q:q + (1 << 26)] - ref).abs().max()) <= 1e-6 * float(alpha.sum()), q
