@@ -22,7 +22,9 @@ namespace svmx {
 int64_t split_pitch(int64_t d) { return (d + SKS - 1) / SKS * SKS; }
 
 // Scratch of the split rows: [n][dp / 32][hi 32 | lo 32] halves (dp = d rounded up to 32, zero
-// padded), the power-of-two row scales and the row norms.
+// padded), the power-of-two row scales and the row norms.  The rows start on a 128-byte boundary
+// whatever the address of the caller's workspace (the 256 bytes more leave room for it): their
+// 16-byte pieces are loaded to LDS, and a row's 128 bytes of a stage are one line.
 int64_t gram_split_scratch_bytes(int64_t n, int64_t d) {
   const int64_t dp = split_pitch(d);
   return 2 * (2 * n * dp) + 8 * n + 256;
@@ -31,8 +33,7 @@ int64_t gram_split_scratch_bytes(int64_t n, int64_t d) {
 SplitX split_views(void *scratch, int64_t n, int64_t d) {
   SplitX s;
   s.dp = split_pitch(d);
-  char *p = static_cast<char *>(scratch);
-  s.rows = reinterpret_cast<_Float16 *>(p);
+  s.rows = reinterpret_cast<_Float16 *>((reinterpret_cast<uintptr_t>(scratch) + 127) & ~(uintptr_t)127);
   s.scale = reinterpret_cast<float *>(s.rows + 2 * n * s.dp);
   s.nrm = s.scale + n;
   return s;

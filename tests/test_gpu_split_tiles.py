@@ -2,6 +2,8 @@
 chunks and the 128-row tiles, feature counts around the 32-feature stages and past what a lane keeps
 in registers, row pitches of every alignment (plain and non-temporal stores), and X at an odd
 address."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -160,3 +162,38 @@ def test_ovo_votes_are_those_of_its_decisions(k, per, m):
             votes[:, j] += dec[:, p] <= 0
             p += 1
     assert np.array_equal(pred.cpu().numpy(), votes.argmax(1))
+
+
+@pytest.mark.parametrize("off", [8, 40, 120, 248])
+def test_workspace_at_any_address(off):
+    """The split rows start on a line of their own wherever the caller's workspace starts (a multiple of 8 bytes,
+    for its doubles): the bits of Gram, decisions and multipliers do not depend on it."""
+    lib = svmx.load()
+    n, m, d = 1500, 140, 70
+    X, T = _x(n, d, 1), _x(m, d, 2)
+    y = torch.where(X[:, 0] + X[:, 1] > 1.0, 1, -1).int()
+    o = svmx.options()
+
+    def ws(size):
+        buf = torch.zeros(int(size) + 512, dtype=torch.uint8, device="cuda")
+        at = -buf.data_ptr() % 256 + off
+        return buf[at:at + int(size)], int(size), buf[at + int(size):]
+
+    w, size, past = ws(lib.svm_gram_workspace_bytes(n, d, C.byref(o)))
+    G = torch.empty((n, n), device="cuda")
+    assert lib.svm_gram(svmx._ptr(X), n, d, 0.05, svmx._ptr(G), n, svmx._ptr(w), size, C.byref(o)) == 0
+    assert torch.equal(G, svmx.svm_gram(X, 0.05)) and not bool(past.any())
+    alpha = torch.empty(n, dtype=torch.float64, device="cuda")
+    b = C.c_double()
+    for kw in (dict(), dict(working_set=8, gram=svmx.GRAM_OFF)):
+        ref = svmx.svm_train(X, y, 1.0, 0.05, 1e-3, **kw)
+        ot = svmx.options(**kw)
+        w, size, past = ws(lib.svm_train_workspace_bytes(n, d, C.byref(ot)))
+        assert lib.svm_train(svmx._ptr(X), svmx._ptr(y), n, d, 1.0, 0.05, 1e-3, svmx._ptr(alpha), C.byref(b), svmx._ptr(w),
+                             size, C.byref(ot), None) == 0
+        assert torch.equal(alpha, ref.alpha) and b.value == ref.b and not bool(past.any())
+    w, size, past = ws(lib.svm_predict_workspace_bytes(n, d, m))
+    dec = torch.empty(m, dtype=torch.float64, device="cuda")
+    assert lib.svm_predict(svmx._ptr(X), svmx._ptr(y), svmx._ptr(alpha), b.value, n, d, 0.05, svmx._ptr(T), m, svmx._ptr(dec),
+                           svmx._ptr(w), size, C.byref(o)) == 0
+    assert torch.equal(dec, svmx.svm_predict(X, y, alpha, b.value, 0.05, T)) and not bool(past.any())

@@ -1,8 +1,9 @@
 """Host checks of index and bit arithmetic that the gfx950 kernels use, compiled with hipcc
 for the host: the upper-triangle tile order of the Gram kernels (csrc/tile_order.hpp) hits every
 tile exactly once, the solver's exchange record (csrc/xchg_record.hpp) round-trips, the
-working-set candidate words (csrc/ws_record.hpp) keep the fp64 order and round-trip, and the rule
-for predictions of few samples (csrc/few_rule.hpp) takes the way that was measured to be faster."""
+working-set candidate words (csrc/ws_record.hpp) keep the fp64 order and round-trip, the rule for
+predictions of few samples (csrc/few_rule.hpp) takes the way that was measured to be faster, and the
+split rows (csrc/gram_split.hip) are aligned wherever their scratch starts."""
 import os
 import subprocess
 
@@ -38,3 +39,8 @@ def test_working_set_candidate_words(tmp_path):
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
 def test_few_samples_rule(tmp_path):
     assert _run("few_rule_check.cpp", tmp_path).startswith("ok")
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
+def test_split_rows_are_aligned(tmp_path):
+    assert _run("split_views_check.cpp", tmp_path).startswith("ok")
