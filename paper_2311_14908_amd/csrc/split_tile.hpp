@@ -82,7 +82,8 @@ __device__ __forceinline__ void split_tile_loaded(SplitStage &S, const char *(&s
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[a][b] = (v4f){0.f, 0.f, 0.f, 0.f};
   for (int64_t st = 1;; ++st) {
-    __syncthreads();  // waits for the loads, too
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's loads to LDS (a barrier alone asks for no wait)
+    __syncthreads();
     split_stage_mma(S, wm, wn, acc);
     __syncthreads();  // this stage's operands have been read
     if (st >= stages) break;
