@@ -1089,6 +1089,7 @@ svm_status svm_train_ovo(const float *X, const int32_t *label, int64_t n, int64_
     probe.X = Xs;
     probe.d = d;
     probe.max_per_wg = max_per_wg;
+    probe.second_order = r.selection == SVM_SELECT_SECOND_ORDER ? 1 : 0;
     HIPCHK(launch_solver(probe, 0, per_thread, p.gram, stream, &capacity));
     if (capacity <= 0) return fail(SVM_ENOMEM, "the solver does not fit on the device");
     if (wg <= capacity || budget <= p.P) break;

@@ -140,6 +140,22 @@ def test_ovo_pairs_equal_standalone_second_order_solves():
         assert out.stats[p]["iterations"] == r.stats["iterations"]
 
 
+@pytest.mark.parametrize("k,per", [(64, 4), (25, 1030)])
+def test_ovo_pairs_beyond_what_the_device_holds_at_once(k, per):
+    """More pairs than workgroups of the second-order kernel fit at once (it needs more registers than the
+    first-order one, whose count does not apply): they run in batches, each as on its own."""
+    X, lab, _, _ = synth.generate(4, n=k * per, m=1, d=12, classes=k)
+    Xd, opt = dev(X), dict(gram=svmx.GRAM_ON, selection=SO, max_iter=40)
+    out = svmx.svm_train_ovo(Xd, dev(lab), k, 10.0, 0.05, 1e-3, **opt)
+    offs, sizes = svmx.ovo_offsets(lab, k)
+    pairs = oracle.ovo_pairs(k)
+    for p in (0, 1, len(pairs) // 2, len(pairs) - 1):
+        idx, y = oracle.ovo_local(lab, *pairs[p])
+        r = svmx.svm_train(dev(X[idx]), dev(y), 10.0, 0.05, 1e-3, **opt)
+        assert torch.equal(out.alpha[offs[p]:offs[p] + sizes[p]], r.alpha)
+        assert out.b[p] == r.b and out.stats[p]["iterations"] == r.stats["iterations"]
+
+
 def test_second_order_takes_no_more_steps_than_mvp_on_c0(c0so):
     """On workload 0 the second-order rule needs fewer steps than the maximal violating pair, on
     both sides (oracle: 424 against 498)."""
