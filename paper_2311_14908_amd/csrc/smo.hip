@@ -415,8 +415,12 @@ __device__ __forceinline__ double so_gain(double ft, double bup, float kut) {
 // This thread's samples and their candidates.  Membership of I_up and I_low is kept per sample and
 // only changes for u and l.  Gram path: as what is added to its f before it is compared, 0 for a
 // member (which also turns -0 into +0), +-infinity otherwise, so offering a sample costs an
-// addition, a compare and three selects a side and no branch.  Row path (FLAGS): as bits, for its
-// registers are needed by the rows.
+// addition, a compare and three selects a side and no branch.  FLAGS: as bits, where the registers are
+// needed: on the row path by the rows, and with 8 samples a thread or more.  With 16 the 64 registers of
+// addends spilled (second-order rule, 500 steps at 2,500 x 64 4.46 -> 3.32 ms, at 4,096 x 10 5.36 ->
+// 3.62; first-order 1.70 -> 1.62); with 8 a CU held two workgroups instead of three, which splits
+// one-vs-one trainings into more batches (36 classes of 1,000, 630 pairs, 2.75 -> 2.16 ms; 10 of 9,000
+// with 16 workgroups a pair 9.26 -> 7.10).
 template <int BS, int PER, bool FLAGS>
 struct Own {
   static constexpr int NP = FLAGS ? 1 : PER;
@@ -528,7 +532,7 @@ __global__ void __launch_bounds__(BS) smo_solve(SolveParams p) {
   const int64_t lim = min(base + (int64_t)P.per_wg, P.n);
   const double C = p.C;
   const bool from_zero = t == 0 && p.warm == 0;
-  Own<BS, PER, !GRAM> own;
+  Own<BS, PER, !GRAM || PER >= 8> own;
   own.ypos = own.mu = own.ml = 0;
   unsigned col[PER];  // Gram path: byte offset of sample k's column in a row of the Gram
 #pragma unroll
