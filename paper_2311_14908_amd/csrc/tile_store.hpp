@@ -110,9 +110,13 @@ __device__ __forceinline__ void store_tile_128_as(float *__restrict__ G, int64_t
           const float(&v)[4] = h ? v2 : v1;
           if (mr >= n) continue;
           float *dst = G + mr * ld + mc;
+          if (mc + 3 < n) {  // one by one these stores are the longest part of an edge tile (3,000 x 16 34.3 us)
+            tile_put4<NT>(v, dst);
+          } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (mc + e < n) tile_put<NT>(v[e], &dst[e]);
+            for (int e = 0; e < 4; ++e)
+              if (mc + e < n) tile_put<NT>(v[e], &dst[e]);
+          }
         }
       }
     }
