@@ -172,12 +172,14 @@ hipError_t launch_gram(const float *X, int64_t n, int64_t d, float gamma, float 
 }
 
 // out[q][j] = K(x_rows[q], x_j), evaluated with the row path's routines (pairs of rows, the
-// sample norms computed here with the routine that fills the solver's norm table).
-template <int V>
+// sample norms computed here with the routine that fills the solver's norm table).  SB samples at a time a
+// group of lanes (no value depends on it): one for unaligned rows of up to 16 features, where a lane has
+// a row of its own and two cost a wave a SIMD (300,000 x 13, 30 rows 131 and 110 us).
+template <int V, int SB = 2>
 __global__ void __launch_bounds__(256) kernel_rows_k(const float *__restrict__ X, int64_t n, int64_t d, double gamma,
                                                       const int64_t *__restrict__ rows, int64_t r,
                                                       float *__restrict__ out) {
-  constexpr int SB = 2, MAXM = ROW_POSITIONS;
+  constexpr int MAXM = ROW_POSITIONS;
   const int64_t q0 = 2 * (int64_t)blockIdx.y;
   const int64_t q1 = q0 + 1 < r ? q0 + 1 : q0;
   const int64_t ru = rows[q0], rl = rows[q1];
@@ -249,6 +251,9 @@ hipError_t launch_kernel_rows(const float *X, int64_t n, int64_t d, double gamma
   const int kind = row_kind_of(X, d);
   if (kind == ROW_F4)
     hipLaunchKernelGGL(kernel_rows_k<ROW_F4>, dim3((unsigned)bx, (unsigned)pairs), dim3(256), 0, s, X, n, d, gamma,
+                       rows, r, out);
+  else if (kind == ROW_F4U && group_size_for(d, kind) == 1)
+    hipLaunchKernelGGL((kernel_rows_k<ROW_F4U, 1>), dim3((unsigned)bx, (unsigned)pairs), dim3(256), 0, s, X, n, d, gamma,
                        rows, r, out);
   else if (kind == ROW_F4U)
     hipLaunchKernelGGL(kernel_rows_k<ROW_F4U>, dim3((unsigned)bx, (unsigned)pairs), dim3(256), 0, s, X, n, d, gamma,

@@ -74,19 +74,22 @@ __device__ __forceinline__ double group_sum(double v, int gs) {
   return v;
 }
 
-// Per-lane operand type T (a float4 of features, or one float) and accumulator type Acc.  load(row, k,
-// d): unit k of a row in memory, clamped to the last; mask(v, k, d): v without the features that
-// are not unit k's (all of them past the row's end).
+// Per-lane operand type T (a float4 of features, or one float) and accumulator type Acc.  at(row, k):
+// unit k of a row in memory, not the last; load(row, k, d): any, clamped to the last; mask(v, k, d): v
+// without the features that are not unit k's (all of them past the row's end).
 template <int V> struct Lane;
 template <> struct Lane<ROW_F4> {
   typedef float4 T;
   typedef float Acc;
+  static __device__ __forceinline__ float4 at(const float *row, int64_t k) {
+    return gp(reinterpret_cast<const float4 *>(row))[k];
+  }
   static __device__ __forceinline__ float4 load(const float *row, int64_t k, int64_t d) {
-    const int64_t units = d >> 2;
-    return gp(reinterpret_cast<const float4 *>(row))[k < units ? k : units - 1];
+    const int64_t units = row_units(d, ROW_F4);
+    return at(row, k < units ? k : units - 1);
   }
   static __device__ __forceinline__ float4 mask(float4 v, int64_t k, int64_t d) {
-    const float m = k < (d >> 2) ? 1.f : 0.f;
+    const float m = k < row_units(d, ROW_F4) ? 1.f : 0.f;
     return make_float4(v.x * m, v.y * m, v.z * m, v.w * m);
   }
   static __device__ __forceinline__ float dot(float4 v, float4 a, float acc) {
@@ -100,6 +103,7 @@ template <> struct Lane<ROW_F4> {
 template <> struct Lane<ROW_SCALAR> {
   typedef float T;
   typedef float Acc;
+  static __device__ __forceinline__ float at(const float *row, int64_t k) { return gp(row)[k]; }
   static __device__ __forceinline__ float load(const float *row, int64_t k, int64_t d) {
     return gp(row)[k < d ? k : d - 1];
   }
@@ -113,6 +117,9 @@ template <> struct Lane<ROW_F4U> {
   typedef float T __attribute__((ext_vector_type(4)));
   typedef T Acc;
   typedef float U __attribute__((ext_vector_type(4), aligned(4)));  // a float4 at any 4-byte address
+  static __device__ __forceinline__ T at(const float *row, int64_t k) {
+    return *(const SVMX_GLOBAL U *)(gp(row) + 4 * k);
+  }
   static __device__ __forceinline__ T load(const float *row, int64_t k, int64_t d) {
     const int64_t o = 4 * k < d - 4 ? 4 * k : d - 4;
     return *(const SVMX_GLOBAL U *)(gp(row) + o);
@@ -141,14 +148,15 @@ template <> struct Lane<ROW_F4U> {
 // with itself (a group of gs lanes; lane `lig` accumulates positions lig, lig+gs, ... in
 // increasing order in fp32, the group sums the partials in fp64).  So |x|^2 + |x|^2 - 2 x.x is
 // exactly 0 for identical rows (K = 1 on the diagonal and between duplicates), and every caller
-// gets the same bits for a row.
+// gets the same bits for a row.  Whole units are neither clamped nor masked (doing so anyway took
+// svm_kernel_rows, which evaluates a norm per sample, from 116 to 125 us at 500 x 784).
 template <int V>
 __device__ __forceinline__ double sq_norm(const float *x, int64_t d, int lig, int gs) {
   const int64_t units = row_units(d, V);
   typename Lane<V>::Acc acc = 0.f;
   for (int64_t k = lig; k < units; k += gs) {
-    const typename Lane<V>::T v = Lane<V>::load(x, k, d);
-    acc = Lane<V>::dot(v, Lane<V>::mask(v, k, d), acc);
+    const typename Lane<V>::T v = V == ROW_F4U ? Lane<V>::load(x, k, d) : Lane<V>::at(x, k);
+    acc = Lane<V>::dot(v, V == ROW_F4U ? Lane<V>::mask(v, k, d) : v, acc);
   }
   return group_sum(Lane<V>::total(acc), gs);
 }
