@@ -505,6 +505,13 @@ __device__ __forceinline__ few_f4u few_load(const float *__restrict__ x, int64_t
   return v;
 }
 
+// exp2(c d2), c d2 <= 0: exp2 of the fp32 part of the exponent, then the rest to first order.
+__device__ __forceinline__ double rbf_of_d2(double c, double d2) {
+  const double x2 = c * (d2 > 0.0 ? d2 : 0.0);
+  const float hi = (float)x2, e2 = __builtin_amdgcn_exp2f(hi);
+  return hi > -150.f ? (double)__builtin_fmaf(e2, 0.6931472f * (float)(x2 - (double)hi), e2) : 0.0;
+}
+
 template <int MQ>
 __global__ void __launch_bounds__(FEW_BS) predict_few_k(const float *__restrict__ T, int64_t m, const float *__restrict__ X,
                                                         int64_t d, const double *__restrict__ alpha_all,
@@ -598,14 +605,7 @@ __global__ void __launch_bounds__(FEW_BS) predict_few_k(const float *__restrict_
         for (int q = 0; q < MQ; ++q) s[q] += __shfl_xor(s[q], o);
       const double coef = coefs[r];
 #pragma unroll
-      for (int q = 0; q < MQ; ++q) {
-        const double d2 = s[q] > 0.0 ? s[q] : 0.0;
-        // exp2 of the fp64 exponent: of its fp32 part, then the rest to first order
-        const double x2 = c * d2;
-        const float hi = (float)x2, e2 = __builtin_amdgcn_exp2f(hi);
-        const float k = hi > -150.f ? __builtin_fmaf(e2, 0.6931472f * (float)(x2 - (double)hi), e2) : 0.f;
-        sum[q] = __builtin_fma(coef, (double)k, sum[q]);
-      }
+      for (int q = 0; q < MQ; ++q) sum[q] = __builtin_fma(coef, rbf_of_d2(c, s[q]), sum[q]);
     }
     __syncthreads();  // rows, coefs and cnt are rewritten
   }
@@ -669,19 +669,45 @@ static hipError_t launch_predict_few(const PredictLaunch &L, hipStream_t s) {
 }
 
 // dec[q * stride + p] = the sum of problem p's (blockIdx.y) split partials - its bias.  A split
-// without a tile wrote nothing.
+// without a tile wrote nothing.  nrm (split-fp16 rows): the norms of the test samples; where one is
+// infinite (squares above the largest float), the tiles' |t|^2 + |x|^2 - 2 t.x is infinite even for t = x,
+// and the wave takes the sample again by differences in fp64, as predict_few does.
 __global__ void __launch_bounds__(64) predict_final_k(const double *__restrict__ part_all, int64_t m,
                                                       const PredPair *__restrict__ pairs, PredPair one,
-                                                      const int64_t *__restrict__ sv_count, double *dec, int64_t stride) {
+                                                      const int64_t *__restrict__ sv_count, double *dec, int64_t stride,
+                                                      const float *__restrict__ nrm, const float *__restrict__ T,
+                                                      const float *__restrict__ X, int64_t d,
+                                                      const int32_t *__restrict__ sv_row_all,
+                                                      const double *__restrict__ sv_coef_all, double c) {
   const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (q >= m) return;
   const PredPair pp = pair_of(pairs, one, blockIdx.y);
   const double *part = part_all + pp.part_off;
-  const int used = (int)min<int64_t>(pp.nsplit, (sv_count[blockIdx.y] + PT - 1) / PT);
+  const int64_t nsv = sv_count[blockIdx.y];
+  const int used = (int)min<int64_t>(pp.nsplit, (nsv + PT - 1) / PT);
   double s = 0.0;
+  if (q < m) {
 #pragma unroll 8
-  for (int k = 0; k < used; ++k) s += part[(int64_t)k * m + q];
-  dec[q * stride + blockIdx.y] = s - pp.b;
+    for (int k = 0; k < used; ++k) s += part[(int64_t)k * m + q];
+  }
+  unsigned long long again = nrm ? __ballot(q < m && nrm[q < m ? q : m - 1] == INFINITY) : 0;
+  while (again) {
+    const int lane = __builtin_ctzll(again);
+    again &= again - 1;
+    const float *t = T + (q - threadIdx.x + lane) * d;
+    double sum = 0.0;
+    for (int64_t v = threadIdx.x; v < nsv; v += 64) {
+      const float *x = X + (int64_t)sv_row_all[pp.sv_off + v] * d;
+      double d2 = 0.0;
+      for (int64_t k = 0; k < d; ++k) {
+        const double f = (double)(x[k] - t[k]);
+        d2 = __builtin_fma(f, f, d2);
+      }
+      sum = __builtin_fma(sv_coef_all[pp.sv_off + v], rbf_of_d2(c, d2), sum);
+    }
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    s = (int)threadIdx.x == lane ? sum : s;
+  }
+  if (q < m) dec[q * stride + blockIdx.y] = s - pp.b;
 }
 
 // Workgroups of a launch at most: of the worst case (every training sample a support vector) most
@@ -762,7 +788,8 @@ hipError_t launch_predict_pairs(const PredictLaunch &L, hipStream_t s) {
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(predict_final_k, dim3((unsigned)((L.m + 63) / 64), (unsigned)L.npairs), dim3(64), 0, s, ws.part,
-                     L.m, p.pairs, p.one, ws.count, L.dec, L.dec_stride);
+                     L.m, p.pairs, p.one, ws.count, L.dec, L.dec_stride, L.split ? ws.split_test.nrm : nullptr, L.T, L.Xtr, L.d,
+                     ws.sv_row, ws.sv_coef, -L.gamma * 1.4426950408889634);
   return hipGetLastError();
 }
 

@@ -90,6 +90,27 @@ def test_predict_edges(n, nsv, m, d, mfma):
     assert torch.equal(dec, again)
 
 
+@pytest.mark.parametrize("mfma", [svmx.MFMA_SPLIT_F16, svmx.MFMA_F32])
+@pytest.mark.parametrize("m,at", [(4, 1), (40, 2), (300, 200), (300, 299)])
+@pytest.mark.parametrize("value", [1e22, -3e30, 1e38])
+def test_predict_of_a_support_vector_whose_squares_overflow(value, m, at, mfma):
+    """A test sample equal to a support vector with K = 1, and to no other with K = 0, where |x|^2 is above the
+    largest float; the other samples' decisions stay those of the other support vectors."""
+    n, d = 500, 20
+    X, T = _x(n, d, 1), _x(m, d, 2)
+    X[7, 3] = value
+    T[at] = X[7]
+    y = torch.where(torch.arange(n, device="cuda") % 3 == 0, 1, -1).int()
+    alpha = torch.rand(n, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(3)) + 0.1
+    dec = svmx.svm_predict(X, y, alpha, 0.5, 0.3, T, gram_mfma=mfma)
+    assert abs(float(dec[at]) - (float(alpha[7]) * int(y[7]) - 0.5)) <= 1e-12
+    rest = alpha.clone()
+    rest[7] = 0.0
+    keep = torch.arange(m, device="cuda") != at
+    ref, tol = _decision64(X, y, rest, 0.5, 0.3, T)
+    assert float((dec - ref)[keep].abs().max()) <= tol
+
+
 @pytest.mark.parametrize("m", [1, 2, 4, 5, 15, 16, 17])
 @pytest.mark.parametrize("n,d", [(1, 1), (127, 5), (129, 16), (4097, 17), (513, 255), (700, 1024), (300, 1025), (9000, 2100)])
 def test_predict_few_samples(n, d, m):
