@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(256) kernel_rows_k(const float *__restrict__ X
       nj[b] = sq_norm<V>(xs[b], d, lig, gs);
     }
     double du[SB], dl[SB];
-    dot_batch<V, SB, MAXM>(xs, nb, xu, xl, d, lig, gs, rp, du, dl);
+    dot_batch<V, SB, MAXM, V == ROW_F4U>(xs, nb, xu, xl, d, lig, gs, rp, du, dl);
     for (int v = lig; v < 2 * SB; v += gs) {
       const int b = v < SB ? v : v - SB;
       if (b >= nb) continue;

@@ -155,8 +155,8 @@ __device__ __forceinline__ double sq_norm(const float *x, int64_t d, int lig, in
   const int64_t units = row_units(d, V);
   typename Lane<V>::Acc acc = 0.f;
   for (int64_t k = lig; k < units; k += gs) {
-    const typename Lane<V>::T v = V == ROW_F4U ? Lane<V>::load(x, k, d) : Lane<V>::at(x, k);
-    acc = Lane<V>::dot(v, V == ROW_F4U ? Lane<V>::mask(v, k, d) : v, acc);
+    const typename Lane<V>::T v = V == ROW_F4U ? Lane<V>::mask(Lane<V>::load(x, k, d), k, d) : Lane<V>::at(x, k);
+    acc = Lane<V>::dot(v, v, acc);
   }
   return group_sum(Lane<V>::total(acc), gs);
 }
@@ -215,7 +215,9 @@ __device__ __forceinline__ void load_block0(typename Lane<V>::T (&v)[SB][MAXM], 
 // products of its positions k = lig, lig+gs, ... in increasing order, so a sample's partials do
 // not depend on SB, on the batch it shares, on where its row is read from, or on which of the
 // two rows is x_u.
-template <int V, int SB, int MAXM, bool XLDS = false>
+// MASKED: the samples may hold values that are not finite (the rows x_u and x_l are always masked, which is
+// enough for finite ones).
+template <int V, int SB, int MAXM, bool XLDS = false, bool MASKED = false>
 __device__ __forceinline__ void dot_partials(const typename Lane<V>::T (&v0)[SB][MAXM], const float *const *xs,
                                              int nb, const float *xu, const float *xl, int64_t d, int lig, int gs,
                                              const RowPair<V, MAXM> &r, typename Lane<V>::Acc (&fu)[SB],
@@ -228,8 +230,9 @@ __device__ __forceinline__ void dot_partials(const typename Lane<V>::T (&v0)[SB]
     fl[s] = 0.f;
 #pragma unroll
     for (int m = 0; m < MAXM; ++m) {  // r.a / r.b are zero past d (X is finite)
-      fu[s] = Lane<V>::dot(v0[s][m], r.a[m], fu[s]);
-      fl[s] = Lane<V>::dot(v0[s][m], r.b[m], fl[s]);
+      const T v = MASKED ? Lane<V>::mask(v0[s][m], lig + (int64_t)m * gs, d) : v0[s][m];
+      fu[s] = Lane<V>::dot(v, r.a[m], fu[s]);
+      fl[s] = Lane<V>::dot(v, r.b[m], fl[s]);
     }
   }
   // Later blocks: MAXL positions at a time (fewer registers than block 0; they occur only for
@@ -251,8 +254,9 @@ __device__ __forceinline__ void dot_partials(const typename Lane<V>::T (&v0)[SB]
       const T am = Lane<V>::mask(a[m], k, d), bm = Lane<V>::mask(b[m], k, d);
 #pragma unroll
       for (int s = 0; s < SB; ++s) {
-        fu[s] = Lane<V>::dot(v[s][m], am, fu[s]);
-        fl[s] = Lane<V>::dot(v[s][m], bm, fl[s]);
+        const T vm = MASKED ? Lane<V>::mask(v[s][m], k, d) : v[s][m];
+        fu[s] = Lane<V>::dot(vm, am, fu[s]);
+        fl[s] = Lane<V>::dot(vm, bm, fl[s]);
       }
     }
   }
@@ -261,13 +265,13 @@ __device__ __forceinline__ void dot_partials(const typename Lane<V>::T (&v0)[SB]
 // Dot products of nb <= SB samples xs[0..nb) with x_u (pu) and x_l (pl), computed by a group
 // of gs lanes: the lanes' fp32 partials (dot_partials) summed over the group in fp64
 // (group_sum).  Called with the whole wave active (nb, gs uniform per group).
-template <int V, int SB, int MAXM>
+template <int V, int SB, int MAXM, bool MASKED = false>
 __device__ __forceinline__ void dot_batch(const float *const *xs, int nb, const float *xu, const float *xl, int64_t d,
                                           int lig, int gs, const RowPair<V, MAXM> &r, double *pu, double *pl) {
   typename Lane<V>::T v[SB][MAXM];
   load_block0<V, SB, MAXM>(v, xs, nb, d, lig, gs);
   typename Lane<V>::Acc fu[SB], fl[SB];
-  dot_partials<V, SB, MAXM>(v, xs, nb, xu, xl, d, lig, gs, r, fu, fl);
+  dot_partials<V, SB, MAXM, false, MASKED>(v, xs, nb, xu, xl, d, lig, gs, r, fu, fl);
 #pragma unroll
   for (int s = 0; s < SB; ++s) {
     pu[s] = group_sum(Lane<V>::total(fu[s]), gs);

@@ -44,3 +44,18 @@ def test_rows_of_any_length_and_alignment(d, off):
         Kp = svmx.svm_kernel_rows(X, 1.0 / d, np.array([u, l])).cpu().numpy().astype(np.float64)
         a, yf = out.alpha.cpu().numpy(), y.numpy().astype(np.float64)
         np.testing.assert_array_equal(f.cpu().numpy(), -yf + (a[u] * yf[u] * Kp[0] + a[l] * yf[l] * Kp[1]))
+
+
+@pytest.mark.parametrize("d", [4, 5, 6, 7, 13, 37, 257])
+def test_an_infinite_feature_counts_once(d):
+    """A feature that two units of a ragged row hold is multiplied once, so an infinite one does not meet the 0 that
+    stands for it in the other unit: K = 0 for a sample at an infinite distance on the far side of the row."""
+    from paper_2311_14908_amd import svmx
+    n = 300
+    X = -torch.rand(n, d, generator=torch.Generator().manual_seed(d)) - 0.1
+    for k in range(d):
+        X[10 + k, k] = float("inf")
+    K = svmx.svm_kernel_rows(X.cuda(), 0.5, np.array([0, 1])).cpu().numpy()
+    far = np.arange(10, 10 + d)
+    assert (K[:, far] == 0.0).all()
+    assert np.isfinite(K).all() and K[0, 0] == 1.0 and K[1, 1] == 1.0
