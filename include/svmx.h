@@ -152,21 +152,27 @@ typedef struct {
   double dual_obj;      /* W(a) = 1/2 sum a - 1/2 sum a y f */
   int32_t gram_used;    /* 1 if the full Gram was precomputed */
   int32_t launches;     /* solver launches (host convergence checks) */
-  double t_gram;        /* seconds of the precompute: the Gram build, or the squared row norms
-                           of the row path */
-  double t_solve, t_finalize, t_total; /* seconds */
+  double t_gram;        /* seconds of the precompute: the Gram build (its split rows are also checked for
+                           values that are not finite), or the squared row norms of the row path, or the
+                           split rows of the working-set row path */
+  double t_solve;       /* seconds from there to the end of the last solver launch (a warm start's
+                           recomputation of f included) */
+  double t_finalize;    /* seconds of the sums at the end (objective, support-vector counts) */
+  double t_total;       /* seconds of the call, on the host's clock */
   double t_kernel;      /* seconds the solver kernel ran, summed over its launches (HIP events on
                            the launch stream) */
   int64_t rounds;       /* working-set rounds (0 for the per-step solver) */
   int32_t resident_rows; /* rows of X each solver workgroup kept in LDS (binary row path) */
   int32_t schedule;     /* binary training: 0 = per-step solver, 1 = working-set rounds, 2 = rounds
                            (the automatic probe), then the per-step solver */
-  double t_upload;      /* seconds of input validation and staging before the precompute: the
-                           labels copied to the host and checked (one-vs-one: and class-sorted),
-                           the problem descriptors copied to the device, the device-side scan of X
-                           for values that are not finite (one-vs-one: and the class-sorted copy of
-                           X).  The inputs themselves are device buffers, so no copy of X over
-                           PCIe is part of any call. */
+  double t_upload;      /* seconds on the host before the precompute is queued.  Binary: queueing the
+                           launch that writes the descriptor, initialises the state and checks labels
+                           and X on the device (the launch itself is in no other time; a warm start's
+                           labels and multipliers are also copied to the host and checked).
+                           One-vs-one: the labels copied to the host and class-sorted, the problem
+                           descriptors and the class order copied to the device.  The inputs
+                           themselves are device buffers, so no copy of X over PCIe is part of any
+                           call. */
 } svm_stats;
 
 /* Fill *o with the defaults above. */

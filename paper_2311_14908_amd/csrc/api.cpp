@@ -403,6 +403,7 @@ struct Run {
   Phases ph;
   hipStream_t stream;
   int32_t launches = 0;
+  bool at_solve = false;  // nothing is queued between the SOLVE mark and the first launch
   double t_kernel = 0.0;  // accumulates over the calls of one training
 };
 
@@ -410,7 +411,7 @@ svm_status input_status(const Run &r, const int32_t *y);
 
 // Launch a solver (launch(&max_coresident) enqueues one launch, finish() what follows each) over
 // problems q0 .. q0 + nprob until none of them is running, or until stop() says so after a launch;
-// one copy and one wait a launch.  The first launch after the SOLVE mark is timed from that mark.
+// one copy and one wait a launch.  A first launch that follows the SOLVE mark is timed from that mark.
 // Returns SVM_OK or a negative status.
 template <class Launch, class Finish, class Stop = NeverStop>
 svm_status run_launches(Run &r, Launch launch, Finish finish, const int32_t *y, int32_t q0, int32_t nprob,
@@ -418,7 +419,7 @@ svm_status run_launches(Run &r, Launch launch, Finish finish, const int32_t *y, 
   std::vector<int64_t> prev(nprob, -1);
   for (;;) {
     int32_t maxres = 0;
-    const int from = r.launches == 0 ? Phases::SOLVE : Phases::KERNEL;
+    const int from = r.launches == 0 && r.at_solve ? Phases::SOLVE : Phases::KERNEL;
     if (from == Phases::KERNEL) HIPCHK(r.ph.mark(from, r.stream));
     hipError_t e = launch(&maxres);
     if (e == hipErrorCooperativeLaunchTooLarge)
@@ -759,6 +760,7 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
     HIPCHK(launch_split_rows(X, n, d, split_views(ws + p.off_split, n, d), stream, nullptr, run.st.d_check()));
   else
     HIPCHK(launch_row_norms(X, n, d, sqn, stream));
+  HIPCHK(run.ph.mark(Phases::SOLVE, stream));
 
   if (r.alpha_init) {
     // what has been launched so far has looked at all of the input; alpha is written only after its verdict
@@ -823,12 +825,12 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
     return launch_finalize(dprob, 1, n, C, reinterpret_cast<double *>(ws + p.off_part), run.st.d_ticket(), run.st.d_fin(),
                            stream);
   };
+  run.at_solve = !r.alpha_init && p.working_set == 0;
   svm_status s1;
   int32_t schedule = p.working_set > 0 ? 1 : 0;  // svm_stats.schedule
   if (p.working_set > 0) {
     HIPCHK(hipMemsetAsync(slots, 0, 8 * p.slot_words, stream));
     HIPCHK(hipMemsetAsync(ws + p.off_slots2, 0, 8 * p.slot2_words, stream));
-    HIPCHK(run.ph.mark(Phases::SOLVE, stream));
     WsParams wp{};
     wp.sp = sp;
     wp.rounds = run.st.d_rounds();
@@ -883,7 +885,6 @@ static svm_status train_impl(const float *X, const int32_t *y, int64_t n, int64_
       s1 = SVM_OK;
     }
   } else {
-    HIPCHK(run.ph.mark(Phases::SOLVE, stream));
     s1 = run_solver(run, sp, finish, y, 0, 1, p.shape.nwg, p.shape.per_thread, p.gram);
   }
   if (s1 != SVM_OK) return s1;
@@ -1140,6 +1141,7 @@ svm_status svm_train_ovo(const float *X, const int32_t *label, int64_t n, int64_
   else
     HIPCHK(launch_row_norms(Xs, n, d, sqn, stream));
   HIPCHK(run.ph.mark(Phases::SOLVE, stream));
+  run.at_solve = true;
   SolveParams sp{};
   sp.probs = dprob;
   sp.wg_prob = wgp;

@@ -70,6 +70,19 @@ def dual(alpha, y, f):
     return 0.5 * a.sum() - 0.5 * float(np.dot(a * yy, ff))
 
 
+def test_times_of_a_warm_start():
+    """The recomputation of f belongs to the solve: t_gram is the row path's squared norms alone, and the solver
+    kernel, which takes no step at the optimum, is a small part of t_solve."""
+    wl, Xd, yd, _ = problem(2, 8000)
+    full = svmx.svm_train(Xd, yd, wl.C, wl.gamma, wl.tol, gram=svmx.GRAM_OFF)
+    for _ in range(2):
+        st = svmx.svm_train(Xd, yd, wl.C, wl.gamma, 2 * wl.tol, gram=svmx.GRAM_OFF, alpha_init=full.alpha).stats
+    assert st["iterations"] == 0
+    assert st["t_gram"] < 0.5 * st["t_solve"] and st["t_kernel"] < 0.5 * st["t_solve"], st
+    ws = svmx.svm_train(Xd, yd, wl.C, wl.gamma, wl.tol, working_set=32).stats
+    assert 0 < ws["t_kernel"] <= ws["t_solve"]
+
+
 def test_recomputed_f_at_the_optimum():
     wl, Xd, yd, _ = problem(3, 20000)
     nn = Xd.shape[0]
