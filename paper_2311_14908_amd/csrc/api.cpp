@@ -521,10 +521,12 @@ svm_status plan_ovo(int64_t n, int64_t d, int32_t k, const Opts &o, OvoPlan *p) 
     return fail(SVM_EINVAL, "second-order selection needs the Gram path");
   Layout L;
   p->off_perm = L.add(4 * n);
-  p->off_xs = L.add(4 * n * d);
+  // the class-sorted copy of X: the split-fp16 rows are gathered from X as they are split
+  const bool split = p->gram && o.gram_mfma == SVM_MFMA_SPLIT_F16;
+  p->off_xs = split ? -1 : L.add(4 * n * d);
   p->off_f = L.add(8 * (int64_t)(k - 1) * n);
   p->off_gram = p->gram ? L.add((int64_t)gram_bytes) : -1;
-  p->off_split = (p->gram && o.gram_mfma == SVM_MFMA_SPLIT_F16) ? L.add(gram_split_scratch_bytes(n, d)) : -1;
+  p->off_split = split ? L.add(gram_split_scratch_bytes(n, d)) : -1;
   p->off_sqn = p->gram ? -1 : L.add(8 * n);
   p->off_status = L.add(status_layout(p->P).bytes);
   p->off_prob = L.add((int64_t)sizeof(Prob) * p->P);
@@ -1021,7 +1023,7 @@ svm_status svm_train_ovo(const float *X, const int32_t *label, int64_t n, int64_
 
   char *ws = static_cast<char *>(workspace);
   int32_t *dperm = reinterpret_cast<int32_t *>(ws + p.off_perm);
-  float *Xs = reinterpret_cast<float *>(ws + p.off_xs);
+  float *Xs = p.off_xs >= 0 ? reinterpret_cast<float *>(ws + p.off_xs) : nullptr;
   double *f = reinterpret_cast<double *>(ws + p.off_f);
   float *G = p.gram ? reinterpret_cast<float *>(ws + p.off_gram) : nullptr;
   Run run;

@@ -75,6 +75,12 @@ def test_workspace_sizes():
     assert ws(1, 16) == -1 and ws(10, 0) == -1
     assert lib.svm_train_ovo_workspace_bytes(60_000, 784, 10, C.byref(_opts())) > 4 * 60_000 ** 2
     assert lib.svm_train_ovo_workspace_bytes(60_000, 784, 1, C.byref(_opts())) == -1
+    # the split-fp16 Gram gathers its rows from X; the other paths hold a class-sorted copy of X
+    ovo = lambda **kw: lib.svm_train_ovo_workspace_bytes(60_000, 784, 10, C.byref(_opts(**kw)))
+    gram, rows = 4 * 60_000 * 60_032, 2 * 2 * 60_000 * 800 + 8 * 60_000
+    assert gram + rows <= ovo() < gram + rows + (16 << 20)
+    assert gram + 4 * 60_000 * 784 <= ovo(gram_mfma=svmx.MFMA_F32)
+    assert ovo(gram=svmx.GRAM_OFF) >= 4 * 60_000 * 784
     bad = _opts()
     bad.struct_size = 12
     assert lib.svm_train_workspace_bytes(100, 4, C.byref(bad)) == -1
