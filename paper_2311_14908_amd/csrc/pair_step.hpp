@@ -73,37 +73,6 @@ __device__ __forceinline__ double wave_extreme(double v) {
   return readlane_d(v, 63);
 }
 
-// Wave-wide min of a and max of b, returned to every lane: the DPP pattern of wave_extreme
-// (quad permutes, row rotations, then the row-15 and row-31 broadcasts into lane 63) with
-// compare-and-select (the values are finite or +-inf, so no NaN canonicalization) and the
-// two chains interleaved round by round.
-__device__ __forceinline__ void wave_minmax(double &a, double &b) {
-#define SVMX_MM_FULL(CTRL)                       \
-  {                                              \
-    const double oa = dpp_full_d<CTRL>(a);       \
-    const double ob = dpp_full_d<CTRL>(b);       \
-    a = oa < a ? oa : a;                         \
-    b = ob > b ? ob : b;                         \
-  }
-#define SVMX_MM_MASK(CTRL, RM)                   \
-  {                                              \
-    const double oa = dpp_mov_d<CTRL, RM>(a);    \
-    const double ob = dpp_mov_d<CTRL, RM>(b);    \
-    a = oa < a ? oa : a;                         \
-    b = ob > b ? ob : b;                         \
-  }
-  SVMX_MM_FULL(0xB1)      // quad_perm [1,0,3,2]
-  SVMX_MM_FULL(0x4E)      // quad_perm [2,3,0,1]
-  SVMX_MM_FULL(0x124)     // row_ror:4
-  SVMX_MM_FULL(0x128)     // row_ror:8
-  SVMX_MM_MASK(0x142, 0xA)  // row_bcast:15 -> rows 1, 3
-  SVMX_MM_MASK(0x143, 0xC)  // row_bcast:31 -> rows 2, 3
-#undef SVMX_MM_FULL
-#undef SVMX_MM_MASK
-  a = readlane_d(a, 63);
-  b = readlane_d(b, 63);
-}
-
 // Wave-wide min of an int, returned to every lane (same DPP pattern).
 __device__ __forceinline__ int wave_min_int(int v) {
   v = min(v, dpp_mov<0xB1, 0xF>(v));
