@@ -69,11 +69,13 @@ def _decision64(X, y, alpha, b, gamma, T):
 
 @pytest.mark.parametrize("mfma", [svmx.MFMA_SPLIT_F16, svmx.MFMA_F32])
 @pytest.mark.parametrize("n,nsv,m,d", [
-    (1, 0, 1, 3), (5, 1, 1, 1), (128, 128, 128, 32), (129, 129, 127, 33), (1023, 127, 129, 40), (1024, 256, 1, 64),
-    (1025, 1025, 257, 17), (2049, 300, 1100, 96), (70001, 40000, 130, 8), (70001, 3, 5, 8), (9000, 8999, 2, 2100)])
+    (1, 0, 17, 3), (5, 1, 18, 1), (128, 128, 128, 32), (129, 129, 127, 33), (1023, 127, 129, 40), (1024, 256, 33, 64),
+    (1025, 1025, 257, 17), (2049, 300, 1100, 96), (70001, 40000, 130, 8), (70001, 3, 129, 8), (9000, 8999, 130, 2100),
+    (70001, 200, 1100, 40), (3000, 0, 1500, 9)])
 def test_predict_edges(n, nsv, m, d, mfma):
     """No, one and a ragged last tile of support vectors; compaction chunks of 1,024 samples and more,
-    empty ones among them; one and many splits; the last chunk's support vectors at the end."""
+    empty ones among them; one and many splits, more splits than tiles with an incomplete group of 8 test tiles; the
+    last chunk's support vectors at the end.  More than 16 samples, so all of it goes by tiles."""
     X, T = _x(n, d, n + d), _x(m, d, m)
     rng = np.random.default_rng(nsv)
     y = torch.from_numpy(np.where(rng.random(n) < 0.5, 1, -1).astype(np.int32)).cuda()
