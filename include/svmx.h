@@ -22,9 +22,11 @@
  *  - "device" pointers are HIP device memory of the current device; "host" pointers are
  *    ordinary host memory.  X arrays are fp32, row-major [rows][d], rows contiguous.
  *  - The caller owns every buffer, including the device workspace, whose size is given by
- *    the matching *_workspace_bytes query.  The library keeps no state between calls
- *    except the loaded code object, a thread-local error message, and (svm_train_static only)
- *    its static device scratch and that scratch's address on each device.
+ *    the matching *_workspace_bytes query; a workspace starts at any multiple of 8 bytes.  The
+ *    library keeps no state between calls except the loaded code object, a thread-local error
+ *    message, a thread-local note of how many workgroups of the last eight solver kernels the
+ *    device holds at once, and (svm_train_static only) its static device scratch and that
+ *    scratch's address on each device.
  *  - All device work is enqueued on options->stream (a hipStream_t; NULL = the null stream).
  *    Every call returns only after its outputs are complete.
  *  - Negative status: nothing was written to the outputs that can be relied upon, nothing
@@ -108,9 +110,11 @@ typedef struct {
                                 the first-order rule, no trace and automatic workgroups, n > 4096:
                                 rounds of q = 64 with a Gram and 128 without (rows of 256 features
                                 or more), else 32, for the first 128 rounds, continued if they took
-                                at least as many pair steps per round as a round costs (Gram path:
-                                10 at q = 64, 4.25 at 32; row path: 12.5 at q = 128, 4.5 at 32,
-                                measured on MI355X), else the per-step solver
+                                at least a fixed number of pair steps per round (Gram path: 10 at
+                                q = 64, 4.25 at 32; row path: 12.5 at q = 128, 4.5 at 32; near what
+                                a round once cost in pair steps, which have become cheaper since,
+                                so rounds may go on where the per-step solver would be up to a
+                                fifth faster), else the per-step solver
                                 takes over from their state (svm_stats.schedule says which); every
                                 other case per-step.  Deterministic: the rule reads the state after
                                 a fixed number of rounds, not the host check cadence.

@@ -52,7 +52,8 @@ __global__ void __launch_bounds__(256) gram_split_k(SplitRows p, int64_t d) {
 // 1,450 TFLOP/s the stage loop reaches, 0.91 ms in all against 1.16 ms with stages staged through
 // registers; 60,000 x 784 7.7 against 9.8 ms), short ones by the stores (100,000 x 32: 40 GB in
 // 7.0 ms).  Four workgroups a CU: one's products run under the others' loads and stores (three:
-// 50,000 x 128 2.07 instead of 2.01 ms, 60,000 x 784 7.88 instead of 7.70).
+// 50,000 x 128 2.07 instead of 2.01 ms, 60,000 x 784 7.88 instead of 7.70); they leave 128 registers,
+// and 5 are spilled (20 bytes a lane, not in the stage loop).
 // In a diagonal tile the cross products h.l and l.h are accumulated in the order of the operand
 // roles, so K(x_r, x_c) and K(x_c, x_r) can differ in the last bit; the upper one (row index <=
 // column index, the role every off-diagonal tile uses) is written to both places, so that

@@ -1009,7 +1009,9 @@ static size_t row_path_lds(const SolveParams &p, int64_t res) {
 // For lane groups of up to 8 lanes (rows of up to 128 features) batches of one are faster
 // (1,000,000 x 16: 25.8 -> 17.5 us a step; 1,000,000 x 64: 55.0 -> 46.0; 600,000 x 128: 55.2 ->
 // 49.1); for wider groups the loads one batch keeps in flight matter more than the spill
-// (batches of one: 600,000 x 256 115 -> 120 us, x 512 214 -> 238, x 784 326 -> 362).
+// (batches of one: 600,000 x 256 115 -> 120 us, x 512 214 -> 238, x 784 326 -> 362).  Units at any
+// address take the same line, which has not been measured for them; they spill more (with 8 samples a
+// thread and batches of two 164 bytes a lane against 128, with 4 samples 48 against 12).
 static bool row_batch_one(const SolveParams &p, int32_t per_thread) {
   return per_thread == 8 && row_kind(p) != ROW_SCALAR && group_size_for(p.d, row_kind(p)) <= 8;
 }
