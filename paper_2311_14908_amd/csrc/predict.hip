@@ -319,8 +319,9 @@ struct PredCols {
 // sums over 16 lanes.)  Short rows are bound by this epilogue's vector instructions (an exp2, a
 // conversion, an fp64 multiply-add and five fp32 ones an entry: about as long as the products of
 // 128 features), long ones by the matrix cores.  Three workgroups a CU: 168 registers, and 10 more
-// spilled (44 bytes a lane, not in the stage loop).  10,000 x 15,000 x 784: 0.56 ms, 1,280 TFLOP/s of fp16 work (1.24 ms before); 4,097 x 30,000 x 127: 131
-// us (202 us; without the next tile's first stage and rows read ahead 140 us).
+// spilled (44 bytes a lane, not in the stage loop).  10,000 x 15,000 x 784: 0.56 ms, 1,280 TFLOP/s of
+// fp16 work (1.24 ms before); 4,097 x 30,000 x 127: 131 us (202 us; without the next tile's first stage
+// and rows read ahead 140 us).
 __global__ void __launch_bounds__(PBS, 3) predict_f16x3_k(SplitX st, int64_t m, SplitX sx,
                                                        const PredPair *__restrict__ pairs, PredPair one, int32_t npairs,
                                                        const int32_t *__restrict__ sv_row_all,
